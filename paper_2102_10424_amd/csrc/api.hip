@@ -293,29 +293,10 @@ gist_status check_csr(const gist_csr_dev* A, int64_t n, const char* what) {
   return GIST_OK;
 }
 
-// The weight gradient dW = X^T D reads both of its operands across their
-// rows (X and D are node-major, the reduction runs over nodes), which the
-// GEMM stages through register transposes at a lower MFMA rate.  For large
-// fp32 products both operands are first transposed into node-contiguous
-// copies, zero-padded to a multiple of 32 nodes, so the GEMM reads
-// K-contiguous tiles and every K step is whole (a ragged last step would
-// take the per-element edge loads); the zero columns add nothing.
-// The copies cost one read and one write of X and D; at c4 sizes (8192 x
-// 4096 x 1633) the product took 921 instead of 1046 us, for three
-// transposes of 18 us each.
-bool transposed_dw(const gist_layer_desc* L, int64_t M, int64_t N, int64_t K) {
-  const int64_t G = L->groups > 1 ? L->groups : 1;
-  return L->dtype == GIST_DTYPE_F32 && G == 1 && M >= 1024 && N >= 1024 && K >= 256 &&
-         (K + 31) / 32 * 32 <= 65535 * 64;   // the transpose grid: padded K in 64-row blocks
-}
-
-int64_t round32(int64_t x) { return (x + 31) / 32 * 32; }
-
-// Workspace layout of the backward pass: [dZ | tmp | gemm scratch | X^T | D^T].
+// Workspace layout of the backward pass: [dZ | tmp | gemm scratch].
 struct BwdPlan {
-  size_t dz = 0, tmp = 0, gemm = 0, ta = 0, tb = 0;
-  bool tdw = false;
-  size_t total() const { return align256(dz) + align256(tmp) + align256(gemm) + align256(ta) + tb; }
+  size_t dz = 0, tmp = 0, gemm = 0;
+  size_t total() const { return align256(dz) + align256(tmp) + gemm; }
 };
 
 BwdPlan plan_bwd(const gist_layer_desc* L) {
@@ -324,24 +305,15 @@ BwdPlan plan_bwd(const gist_layer_desc* L) {
   const int64_t n = y.n, n_in = y.n_in, si = y.si, so = y.so, G = y.G;
   if (L->act == GIST_ACT_RELU && !(L->flags & GIST_LAYER_DZ_IN)) p.dz = fbytes(n, G * so);
   const int order = resolve_order(L);
-  int64_t wm, wk;   // dW = X^T D: M x so, reduced over K nodes
   if (L->kind == GIST_LAYER_SAGE_MEAN || order == GIST_ORDER_AGG_FIRST) {
     p.tmp = fbytes(n, G * si);  // dP = dZ W^T (W_neigh for SAGE)
-    p.gemm = std::max(gist::gemm_workspace(y.wrows, so, n, L->dtype, G),
+    // dW = X^T dZ, X = [H | Abar H] for SAGE: rows in two parts
+    p.gemm = std::max(gist::gemm_workspace(y.wrows, so, n, L->dtype, G, y.wrows > si ? si : 0),
                       gist::gemm_workspace(n, y.wrows, so, L->dtype, G));
-    wm = y.wrows;
-    wk = n;
   } else {
     p.tmp = fbytes(n_in, G * so);  // Abar^T dZ
     p.gemm = std::max(gist::gemm_workspace(si, so, n_in, L->dtype, G),
                       gist::gemm_workspace(n_in, si, so, L->dtype, G));
-    wm = si;
-    wk = n_in;
-  }
-  p.tdw = transposed_dw(L, wm, so, wk);
-  if (p.tdw) {
-    p.ta = fbytes(wm, round32(wk));
-    p.tb = fbytes(so, round32(wk));
   }
   return p;
 }
@@ -352,7 +324,7 @@ size_t plan_fwd(const gist_layer_desc* L) {
   if (L->kind == GIST_LAYER_GCN && order == GIST_ORDER_XFORM_FIRST)
     return align256(fbytes(y.n_in, y.G * y.so)) +
            gist::gemm_workspace(y.n_in, y.so, y.si, L->dtype, y.G);
-  return gist::gemm_workspace(y.n, y.so, y.wrows, L->dtype, y.G);
+  return gist::gemm_workspace(y.n, y.so, y.wrows, L->dtype, y.G, 0, y.wrows > y.si ? y.si : 0);
 }
 
 }  // namespace
@@ -470,9 +442,6 @@ gist_status layer_bwd(gist_ctx* ctx, const gist_layer_desc* L, const gist_csr_de
   float* tmp = reinterpret_cast<float*>(base + align256(p.dz));
   void* gws = base + align256(p.dz) + align256(p.tmp);
   const size_t gbytes = p.gemm;
-  float* tA = reinterpret_cast<float*>(base + align256(p.dz) + align256(p.tmp) +
-                                       align256(p.gemm));
-  float* tB = reinterpret_cast<float*>(reinterpret_cast<char*>(tA) + align256(p.ta));
   const float* dZ = dH_out;
   if (relu && !dz_in) {
     GIST_TRY(gist::relu_mask(st, n * G * so, dH_out, H_out, dZbuf));
@@ -493,20 +462,6 @@ gist_status layer_bwd(gist_ctx* ctx, const gist_layer_desc* L, const gist_csr_de
     // dW_g = [H_g | Abar H_g]^T dZ_g (SAGE) or (Abar H_g)^T dZ_g: element (r, k) of the
     // transposed activation is act[k * ld + r]
     auto weight_grad = [&]() -> gist_status {
-      if (p.tdw) {   // node-contiguous copies: [H | Abar H]^T (wrows x n) and dZ^T (so x n)
-        const int64_t n32 = round32(n);
-        if (sage) {
-          GIST_TRY(gist::transpose(st, H, n, si, y.ld_in, tA, n32));
-          GIST_TRY(gist::transpose(st, agg_save, n, si, y.ld_in, tA + si * n32, n32));
-        } else {
-          GIST_TRY(gist::transpose(st, agg_save, n, si, y.ld_in, tA, n32));
-        }
-        GIST_TRY(gist::transpose(st, dZ, n, so, y.ld_out, tB, n32));
-        gist::Operand at, bt;
-        at.p0 = tA; at.ld0 = n32; at.k_major = true;
-        bt.p0 = tB; bt.ld0 = n32; bt.k_major = true;
-        return gist::gemm(st, y.wrows, so, n32, at, bt, wout, L->dtype, gws, gbytes, 1, n);
-      }
       gist::Operand a;
       a.k_major = false;
       if (sage) {
@@ -546,15 +501,6 @@ gist_status layer_bwd(gist_ctx* ctx, const gist_layer_desc* L, const gist_csr_de
   // dH_g = T_g W_g^T
   GIST_TRY(spmm_out(st, y, AT, n_in, n, dZ, y.gs_out, tmp, y.gs_out_in, false));
   auto weight_grad = [&]() -> gist_status {
-    if (p.tdw) {   // node-contiguous copies H^T (si x n_in) and T^T (so x n_in)
-      const int64_t n32 = round32(n_in);
-      GIST_TRY(gist::transpose(st, H, n_in, si, y.ld_in, tA, n32));
-      GIST_TRY(gist::transpose(st, tmp, n_in, so, y.ld_out, tB, n32));
-      gist::Operand at, bt;
-      at.p0 = tA; at.ld0 = n32; at.k_major = true;
-      bt.p0 = tB; bt.ld0 = n32; bt.k_major = true;
-      return gist::gemm(st, si, so, n32, at, bt, wout, L->dtype, gws, gbytes, 1, n_in);
-    }
     gist::Operand a;
     a.p0 = H; a.ld0 = y.ld_in; a.gs0 = y.gs_in; a.k_major = false;
     gist::Operand g;

@@ -1,43 +1,51 @@
-// Dense contractions of the sub-GCN layer on the MFMA matrix cores.
+// Dense contractions of the sub-GCN layer on the bf16 matrix cores.
 //
 // C (M x N) = act(A (M x K) * B (K x N)) for the three products of eq. (2)
 // and its backward pass: the forward transform (Abar H) W (for GraphSAGE
 // [H | Abar H] [W_self; W_neigh]), the weight gradient (Abar H)^T dZ and the
 // input gradient dZ W^T.  Operands are read straight from the row-major
-// activations and weights in whichever orientation the product needs (see
-// Operand in gist_internal.h), so no transpose is ever materialised.
+// activations and weights in whichever orientation the product needs.
 //
-// Tiling (gfx950, wave64): a 256-thread block computes a 128 x 128 tile of C;
-// each of its four waves owns a 64 x 64 quadrant = 2 x 2 MFMA tiles of
-// 32 x 32.  K advances in steps of 32 through double-buffered LDS tiles that
-// always hold both operands K-contiguous ([row][k], padded), so every lane
-// fetches its MFMA operands with one 16-byte LDS read per 4 MFMAs.
+// fp32 products, exact to fp32 level: a float has 24 significant bits, so it
+// is the exact sum of three bf16 numbers, hi = bf16(x), mid = bf16(x - hi),
+// lo = bf16(x - hi - mid), each rounded to nearest (both differences are
+// exact).  A product is then
+//   a b = hi hi' + hi mid' + mid hi' + hi lo' + mid mid' + lo hi' + (terms
+//   below 2^-25 |a b| each),
+// six bf16 products accumulated in fp32 by v_mfma_f32_32x32x16_bf16.  The
+// bf16 unit multiplies 16 times as fast as the fp32 one, so six products
+// still have 2.7 times its rate (419 against 157 TFLOP/s).  The split is made
+// in registers on the way to LDS, so every value is split once per tile that
+// uses it and memory sees the fp32 operands only.
 //
-// fp32: v_mfma_f32_32x32x2_f32.  For step s of an 8-wide K chunk, lane l
-// supplies A[i][4 h + s] and B[4 h + s][j] with i = j = l mod 32, h = l / 32:
-// the two K slots of the instruction are mapped onto K columns 4h + s, which
-// is a relabelling of the K sum and leaves the product unchanged.
+// What bounds it: power.  A loop of nothing but these MFMAs on random data
+// holds 1,720 TFLOP/s (287 of fp32 products) at 1.8 GHz, on zeros 2,440; the
+// 256 x 256 tiles keep the matrix cores busy 72% of the cycles at 1.77 GHz.
+// On the products of a 4,096-wide GraphSAGE layer with 1,630 nodes (109 GFLOP
+// each), the fp32 matrix instruction took 985 / 985 / 950 us (forward, dH,
+// dW; back to back, hot) and this 620 / 610 / 600; for 512 x 512 weights
+// and 20,000 nodes 134 -> 83 us; a 1,536 x 64 product over K = 602 27 -> 11.
 //
-// bf16-input: the same tile walk, operands rounded to bf16 (nearest-even)
-// when staged into LDS, v_mfma_f32_32x32x16_bf16 with fp32 accumulation.
+// Non-finite values: the split of an Inf or NaN (or of a value that rounds to
+// Inf in bf16) leaves NaN in the tile, so a wave whose accumulators hold
+// anything non-finite recomputes its block with the fp32 matrix instruction
+// straight from memory; finite inputs never take that path unless the
+// product overflows.
 //
-// Work distribution (stream-K): the (tile, K step) iterations of the whole
-// product are dealt out in equal contiguous ranges to a fixed grid of 512
-// workgroups (two per CU on 256 CUs), so the machine stays evenly loaded
-// whatever the tile count -- M = 1,633 gives only 416 or 832 tiles, which
-// whole-tile scheduling would spread over 1.6 rounds.  A tile whose K range
-// is split between workgroups is written as partial tiles to the workspace
-// and summed by a second kernel in workgroup order: deterministic, and no
-// workgroup ever waits on another.  Products with plenty of tiles use one
-// whole tile per workgroup and skip the second kernel.  Products with few
-// tiles and a long K (a weight gradient reduced over many nodes) split K
-// into slices dealt out slice-major, so that the workgroups an XCD runs
-// together share each K range's operand rows in L2.  For N <= 64 the two
-// waves whose columns would lie past the matrix take the second half of
-// every K step instead (see NARROW below).
+// bf16-input products with M or N below 512 run here too (one product of the
+// rounded operands, gemm_small_kernel<1, ...>); larger ones in gemm_bf16.hip.
+//
+// Work distribution: tiles are whole where there are enough of them.  The
+// tiles of the last, partly filled round (or all, where K is beyond 4,096)
+// are cut in K, all at the same steps, slice-major, so that the workgroups an
+// XCD runs together share each K range's operand rows in L2; what is left of
+// each tile is dealt out in runs of the same length.  Partial tiles go to
+// the workspace and a second kernel sums them in K order: deterministic, and
+// no workgroup ever waits on another.
 
 #include <algorithm>
 #include <cstdio>
+#include <type_traits>
 
 #include "common.cuh"
 #include "gemm_common.cuh"
@@ -48,738 +56,970 @@ namespace gist {
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 
-constexpr int BM = 128, BN = 128, BK = 32;
-constexpr int LDK = BK + 4;        // fp32 LDS row stride, [row][k] layout (floats)
-constexpr int kTileF = BM * LDK;   // floats per fp32 operand tile
-constexpr int KSH = 64;            // bf16 K step: two 32-wide load sub-tiles
-constexpr int LDKH = KSH + 8;      // bf16 LDS row stride (halves)
-constexpr int kThreads = 256;
+constexpr int KS = 16;         // K per step: one bf16 MFMA
 
-struct OpDev {
+// Operand view: element (r, k) at p[r * ld + k] (K contiguous) or
+// p[k * ld + r]; p1 takes over at the segment boundary (along K or rows).
+struct SOp {
   const float* p0;
   const float* p1;
-  int64_t ld0, ld1, split;
-  int64_t gs0, gs1;   // group strides of p0 / p1
-
-  __device__ __forceinline__ OpDev group(int64_t g) const {
-    OpDev o = *this;
-    o.p0 += g * gs0;
-    o.p1 += g * gs1;
-    return o;
-  }
+  int64_t ld;
+  int64_t gs0, gs1;
 };
 
-struct OutDev {
+struct SOut {
   float* c0;
   float* c1;
   int64_t ldc0, ldc1, c_split;
-  int relu;
   int64_t gs0, gs1;
-  int sgd;     // C <- fmaf(-lr, product, C): a fused SGD step on weights in C
-  float lr;
-  const float* mask;   // C <- 0 where mask <= 0 (c0 columns only), or null
+  const float* mask;
   int64_t ldm, gsm;
+  float lr;
+  int relu, sgd;
+};
 
-  __device__ __forceinline__ OutDev group(int64_t g) const {
-    OutDev o = *this;
-    o.c0 += g * gs0;
-    o.c1 += g * gs1;
-    if (mask) o.mask += g * gsm;
-    return o;
+// Work of one product: tiles of all groups, the first `whole` of them one
+// workgroup each; the others (`ragged` of them) cut at the same K steps:
+// `full` slices of `ipw` steps, slice-major, and the `rem` steps left of
+// every tile dealt out in runs of ipw.
+struct SSched {
+  int64_t tiles, whole, ragged;
+  int64_t tpg;                 // tiles per group
+  int tiles_m, tiles_n, tm0;   // tm0: tile rows of the first row segment
+  int nk, nf0, nf;             // K steps in all; whole ones of the first K segment, of both
+  int full, ipw, rem;
+  int parts;                   // partial slots per ragged tile (0: nothing is split)
+};
+
+__device__ __forceinline__ unsigned pk_bf16(float a, float b) {
+  return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2){a, b}, bf16x2));
+}
+
+// Four values into their NP bf16 planes.
+template <int NP>
+__device__ __forceinline__ void split4(const float (&x)[4], uintx2 (&pl)[NP]) {
+  float r[4] = {x[0], x[1], x[2], x[3]};
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const unsigned u = pk_bf16(r[2 * h], r[2 * h + 1]);
+      pl[p][h] = u;
+      if (p + 1 < NP) {
+        r[2 * h] -= __builtin_bit_cast(float, u << 16);
+        r[2 * h + 1] -= __builtin_bit_cast(float, u & 0xffff0000u);
+      }
+    }
+  }
+}
+
+// LDS tile of one operand: plane-major, then blocks of 32 rows: 16-byte
+// chunks (8 K) q = 0, 1 of the 32 rows, 1 KB per block.  The row order inside
+// a block makes the fragment reads and both kinds of staging writes free of
+// bank conflicts.
+__device__ __forceinline__ int lds_slot(int r, int q) { return (r ^ ((r >> 3) & 1)) ^ (q * 4); }
+template <int ROWS>
+__device__ __forceinline__ int lds_off(int row, int q) {
+  return (row >> 5) * 1024 + q * 512 + lds_slot(row & 31, q) * 16;
+}
+template <int ROWS>
+constexpr int plane_bytes() { return ROWS * 32; }
+
+// One operand's share of a K step, held in registers between its load and
+// its split.  Groups of four consecutive K of one row.
+//   K contiguous: row (t >> 2) + 64 i, K 4 (t & 3): V = 4, 2 or 1 floats per load.
+//   Row contiguous, V >= 2: two rows by four K, one 8-byte load per K.
+//   Row contiguous, V = 1: one row by four K.
+template <int NP, bool KM, int V, int ROWS, int THR, int KW, typename OFF>
+struct Stage {
+  static constexpr int NG = ROWS * (KW / 4) / THR;     // groups per thread
+  static constexpr bool PAIR = !KM && V >= 2 && KW == 16;
+  static constexpr int GP = PAIR ? 2 : 1;              // groups per load item
+  static constexpr int NI = NG / GP;
+  float v[NG][4];
+  OFF off[NI];
+
+  __device__ __forceinline__ static void item(int t, int i, int& row, int& kk) {
+    const int x = t + THR * i;
+    constexpr int L = KW / 4;   // lanes per row
+    if constexpr (KM) { row = t / L + (THR / L) * i; kk = 4 * (t % L); }
+    else if constexpr (PAIR) { row = 2 * ((x >> 1) % (ROWS / 2)); kk = 8 * (x / ROWS) + 4 * (x & 1); }
+    else if constexpr (KW == 16) { row = (x >> 1) % ROWS; kk = 8 * (x / (2 * ROWS)) + 4 * (x & 1); }
+    else { row = x % ROWS; kk = 4 * (x / ROWS); }
+  }
+  __device__ __forceinline__ void init(int64_t ld, int rows_left, int t) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      int row, kk;
+      item(t, i, row, kk);
+      if constexpr (KM)
+        off[i] = static_cast<OFF>(min(row, rows_left - 1)) * static_cast<OFF>(ld * 4) + 4 * kk;
+      else
+        off[i] = static_cast<OFF>(4 * min(row, rows_left - (PAIR ? 2 : 1))) +
+                 static_cast<OFF>(kk) * static_cast<OFF>(ld * 4);
+    }
+  }
+  // base: the step's first element of the tile's first row; klim >= 1 values
+  // of K exist from there on.  A load past them (EDGE only) reads the last ones.
+  template <bool EDGE>
+  __device__ __forceinline__ void load(int i, const char* base, OFF ld4, int klim, int t) {
+    {
+      int row, kk;
+      item(t, i, row, kk);
+      if constexpr (KM) {
+#pragma unroll
+        for (int j = 0; j < 4; j += V) {
+          const char* p = EDGE ? base + (off[i] + static_cast<OFF>(4 * (min(kk + j, klim - V) - kk)))
+                               : base + off[i] + 4 * j;
+          if constexpr (V == 4) {
+            const floatx4 x = *reinterpret_cast<const floatx4*>(p);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[i][q] = x[q];
+          } else if constexpr (V == 2) {
+            const floatx2 x = *reinterpret_cast<const floatx2*>(p);
+            v[i][j] = x[0];
+            v[i][j + 1] = x[1];
+          } else {
+            v[i][j] = *reinterpret_cast<const float*>(p);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const char* p = EDGE ? base + (off[i] + static_cast<OFF>(min(kk + j, klim - 1) - kk) * ld4)
+                               : base + j * static_cast<int64_t>(ld4) + off[i];
+          if constexpr (PAIR) {
+            const floatx2 x = *reinterpret_cast<const floatx2*>(p);
+            v[2 * i][j] = x[0];
+            v[2 * i + 1][j] = x[1];
+          } else {
+            v[i][j] = *reinterpret_cast<const float*>(p);
+          }
+        }
+      }
+    }
+  }
+  // split group g into the three planes of the LDS tile S (EDGE: K values from
+  // klim on are zero)
+  template <bool EDGE, bool SIGN>
+  __device__ __forceinline__ void store(char* S, int g, int klim, float sg, int t) const {
+    int row, kk;
+    item(t, g / GP, row, kk);
+    if constexpr (PAIR) row += g & 1;
+    float x[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      x[j] = !EDGE || kk + j < klim ? v[g][j] : 0.f;
+      if (SIGN) x[j] *= sg;
+    }
+    uintx2 pl[NP];
+    split4<NP>(x, pl);
+    char* d = S + (KW > 16 ? (kk >> 4) * (NP * plane_bytes<ROWS>()) : 0) + lds_off<ROWS>(row, (kk >> 3) & 1) +
+              ((kk >> 2) & 1) * 8;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) *reinterpret_cast<uintx2*>(d + p * plane_bytes<ROWS>()) = pl[p];
   }
 };
 
-// Element (r, k) of an operand; r < R and k < K are checked by the caller.
-template <bool KMAJ>
-__device__ __forceinline__ float op_elem(const OpDev& o, int64_t r, int64_t k) {
-  if constexpr (KMAJ) {
-    return k < o.split ? o.p0[r * o.ld0 + k] : o.p1[r * o.ld1 + (k - o.split)];
-  } else {
-    return r < o.split ? o.p0[k * o.ld0 + r] : o.p1[k * o.ld1 + (r - o.split)];
-  }
-}
-
-// Thread -> (row, k) of the 4-float group it stages, for a 128 x 32 tile.
-//   K-contiguous operands: 8 threads cover one row's 32 K values (128 B).
-//   Row-contiguous, scalar: consecutive threads take consecutive rows at one
-//     K and read 4 K values each.
-//   Row-contiguous, vector: each thread owns a 4 x 4 block (rows 4g..4g+3,
-//     K values 4q..4q+3) and loads it as 4 row vectors, one per K value;
-//     group i is the vector at K value 4q + i, transposed into rows when
-//     staged.  Lane bits (0 | 1-2 | 3-5) of a wave pick (g mod 2 | q mod 4 |
-//     g / 2 mod 8); the wave picks g / 16 and q / 4.  Each run of eight
-//     lanes (one LDS write pass) then holds both row-block parities times
-//     four K groups, so its 16-byte stores into the [row][k] tile (row
-//     stride LDK = 36 floats) land in eight distinct groups of four banks;
-//     with consecutive row blocks per run they fell into two (4-way
-//     conflicts).  Sixteen lanes still read 256 contiguous bytes per K value.
-template <bool KMAJ, bool VEC>
-__device__ __forceinline__ void tile_coord(int i, int& rr, int& kk) {
-  const int idx = threadIdx.x + kThreads * i;
-  if constexpr (KMAJ) {
-    rr = idx >> 3;
-    kk = (idx & 7) * 4;
-  } else if constexpr (VEC) {
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-    rr = 4 * ((l & 1) + 2 * ((l >> 3) & 7) + 16 * (w & 1));
-    kk = 4 * (((l >> 1) & 3) + 4 * (w >> 1)) + i;
-  } else {
-    rr = idx & 127;
-    kk = (idx >> 7) * 4;
-  }
-}
-
-// Stage a 128 x 32 tile (rows r0.., k0..) of an operand into registers:
-// 4 groups of 4 consecutive K values per thread.
-//
-// Full K tiles (FULLK: k0 + 32 <= K) take a branch-free path: rows past the
-// operand's edge read a clamped (valid) row, so the loads of a tile issue
-// back to back with no wait.  Only the last, partial K tile of a split checks
-// every element (it must contribute exact zeros beyond K).
-template <bool KMAJ, bool VEC, bool FULLK>
-__device__ __forceinline__ void load_tile(const OpDev& o, int64_t R, int64_t K, int64_t r0,
-                                          int64_t k0, floatx4 (&reg)[4]) {
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int rr, kk;
-    tile_coord<KMAJ, VEC>(i, rr, kk);
-    const int64_t r = r0 + rr, k = k0 + kk;
-    floatx4 v = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (!KMAJ && VEC) {
-      // 4 consecutive rows at one K: a 16-byte load along the contiguous dim.
-      // The vector path requires split % 128 == 0, so the whole tile lies on
-      // one side of the split and the pointer choice is uniform.
-      const bool lo = r0 < o.split;
-      const float* base = lo ? o.p0 : o.p1 - o.split;
-      const int64_t ld = lo ? o.ld0 : o.ld1;
-      if constexpr (FULLK) {
-        const int64_t rc = r < R ? r : R - 4;  // R % 4 == 0 on this path
-        v = *reinterpret_cast<const floatx4*>(base + k * ld + rc);
-      } else {
-        if (k < K) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (r + q < R) v[q] = base[k * ld + r + q];
-        }
-      }
-    } else {
-      const bool rin = r < R;
-      const int64_t rc = rin ? r : R - 1;
-      if constexpr (FULLK) {
-        if constexpr (KMAJ && VEC) {
-          // split % 128 == 0: the whole K step lies on one side of the split
-          const bool lo = k0 < o.split;
-          const float* base = lo ? o.p0 : o.p1 - o.split;
-          const int64_t ld = lo ? o.ld0 : o.ld1;
-          v = *reinterpret_cast<const floatx4*>(base + rc * ld + k);
-        } else if constexpr (KMAJ) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = op_elem<KMAJ>(o, rc, k + q);
-        } else {
-          const float* base = rc < o.split ? o.p0 + rc : o.p1 + (rc - o.split);
-          const int64_t ld = rc < o.split ? o.ld0 : o.ld1;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) v[q] = base[(k + q) * ld];
-        }
-        // rows past the edge keep the clamped row's (finite) values: they only
-        // feed output rows / columns the epilogue never stores
-      } else {
-        if (rin) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (k + q < K) v[q] = op_elem<KMAJ>(o, r, k + q);
-        }
-      }
-    }
-    reg[i] = v;
-    (void)t;
-  }
-}
-
-// Transpose a row-vector 4 x 4 block (reg[i][j] = element (rr + j, kk + i))
-// into row order (out[j][i]).
-__device__ __forceinline__ void transpose4(const floatx4 (&reg)[4], floatx4 (&out)[4]) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) out[j][i] = reg[i][j];
-}
-
-template <bool KMAJ, bool VEC>
-__device__ __forceinline__ void store_tile_f32(float* lds, const floatx4 (&reg)[4]) {
-  if constexpr (!KMAJ && VEC) {
-    floatx4 rows[4];
-    transpose4(reg, rows);
-    int rr, kk;
-    tile_coord<KMAJ, VEC>(0, rr, kk);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) *reinterpret_cast<floatx4*>(lds + (rr + j) * LDK + kk) = rows[j];
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int rr, kk;
-      tile_coord<KMAJ, VEC>(i, rr, kk);
-      *reinterpret_cast<floatx4*>(lds + rr * LDK + kk) = reg[i];
-    }
-  }
-}
-
-// MFMA operand fragment: the 4 K values k0 .. k0+3 of tile row `row`.
-__device__ __forceinline__ floatx4 frag_f32(const float* lds, int row, int k0) {
-  return *reinterpret_cast<const floatx4*>(lds + row * LDK + k0);
-}
-
-// Round-to-nearest-even fp32 -> bf16 (gfx950 converts in hardware).
-__device__ __forceinline__ unsigned short f2bf(float f) {
-  return __builtin_bit_cast(unsigned short, static_cast<__bf16>(f));
-}
-
-template <bool KMAJ, bool VEC>
-__device__ __forceinline__ void store_tile_bf16(unsigned short* lds, const floatx4 (&reg)[4],
-                                                int koff) {
-  auto put = [&](int rr, int kk, const floatx4& v) {
-    ushort4 h;
-    h.x = f2bf(v[0]);
-    h.y = f2bf(v[1]);
-    h.z = f2bf(v[2]);
-    h.w = f2bf(v[3]);
-    *reinterpret_cast<ushort4*>(lds + rr * LDKH + koff + kk) = h;
-  };
-  if constexpr (!KMAJ && VEC) {
-    floatx4 rows[4];
-    transpose4(reg, rows);
-    int rr, kk;
-    tile_coord<KMAJ, VEC>(0, rr, kk);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) put(rr + j, kk, rows[j]);
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int rr, kk;
-      tile_coord<KMAJ, VEC>(i, rr, kk);
-      put(rr, kk, reg[i]);
-    }
-  }
-}
-
-struct Sched {
-  int64_t T;        // total iterations = tiles * nk (tiles of all groups)
-  int64_t ipw;      // iterations per workgroup (stream-K)
-  int nk;           // K steps per tile
-  int tiles_m, tiles_n;
-  int64_t tpg;      // tiles per group (tiles_m * tiles_n)
-  int64_t tiles;    // tiles of all groups
-  int64_t spu;      // > 0: K-slice-major split, K steps per slice; 0: stream-K
-};
-
-__device__ __forceinline__ float* out_ptr(const OutDev& C, int64_t row, int64_t col) {
+__device__ __forceinline__ float* s_ptr(const SOut& C, int64_t row, int64_t col) {
   return col < C.c_split ? C.c0 + row * C.ldc0 + col : C.c1 + row * C.ldc1 + (col - C.c_split);
 }
-
-__device__ __forceinline__ void store_out(const OutDev& C, int64_t row, int64_t col, float v) {
+__device__ __forceinline__ void s_store(const SOut& C, int64_t row, int64_t col, float v) {
   if (C.relu) v = fmaxf(v, 0.f);
   if (C.mask && col < C.c_split && !(C.mask[row * C.ldm + col] > 0.f)) v = 0.f;
-  float* p = out_ptr(C, row, col);
+  float* p = s_ptr(C, row, col);
   if (C.sgd) v = fmaf(-C.lr, v, *p);
   *p = v;
 }
 
-// Two resident blocks per CU where that fits in registers without spilling
-// (fp32 with vector loads on both operands, or both K-contiguous).
-template <bool AK, bool BK_, bool AV, bool BV, bool BF16>
-constexpr int min_blocks() { return (!BF16 && ((AV && BV) || (AK && BK_))) ? 2 : 1; }
+// K step j: its first K, the K values it has and its segment.  The whole
+// steps of both segments come first, then each segment's partial step.
+template <int KW>
+__device__ __forceinline__ void k_step(const SSched& S, int64_t K, int64_t ksplit, int j, int64_t& k0,
+                                       int& klim, bool& second) {
+  if (j < S.nf) {
+    second = j >= S.nf0;
+    k0 = second ? ksplit + static_cast<int64_t>(j - S.nf0) * KW : static_cast<int64_t>(j) * KW;
+    klim = KW;
+  } else {
+    second = j > S.nf || ksplit % KW == 0;
+    k0 = second ? K - (K - ksplit) % KW : ksplit - ksplit % KW;
+    klim = static_cast<int>((second ? K : ksplit) - k0);
+  }
+}
 
-// Double-buffered MFMA fragments (16 more VGPRs) where the variant still
-// fits two waves per SIMD with them.
-template <bool AK, bool BK_, bool AV, bool BV>
-constexpr bool kPipeFrag() { return AV && BV && AK == BK_; }
+// The (tile, K range) runs of one workgroup.
+struct Units {
+  int64_t tile = 0;
+  int kb = 0, ke = 0, part = 0;
+  int64_t it = 0, it_end = 0;      // remainder region: over (ragged tile, remaining step)
+  bool one = false, remainder = false;
 
-// NARROW (fp32, N <= 64): the tile's columns 64..127 lie past the matrix, so
-// the two waves that would own them take half of every K step instead --
-// waves wn = 0 the step's 8-wide K chunks 0-1, waves wn = 1 chunks 2-3, all
-// on columns 0..63 -- and the two halves are added through LDS before the
-// epilogue (a split of K inside the workgroup, always summed in the same
-// order).  Each step then costs half the MFMA time per wave.
-template <bool AK, bool BK_, bool AV, bool BV, bool BF16, bool NARROW>
-__global__ __launch_bounds__(kThreads, (min_blocks<AK, BK_, AV, BV, BF16>())) void gemm_kernel(int64_t M, int64_t N, int64_t K,
-                                                        OpDev A, OpDev B, OutDev C, Sched S,
-                                                        float* partials) {
-  static_assert(!(NARROW && BF16), "the narrow split is an fp32 variant");
-  constexpr int kStage = BF16 ? 0 : 2 * kTileF;    // floats per fp32 stage (A + B)
-  constexpr int kStageH = BF16 ? 2 * BM * LDKH : 0;
-  __shared__ __attribute__((aligned(16))) float lds_f[BF16 ? 1 : 2 * kStage];
-  __shared__ __attribute__((aligned(16))) unsigned short lds_h[BF16 ? 2 * kStageH : 1];
+  __device__ __forceinline__ explicit Units(const SSched& S) {
+    const int64_t w = blockIdx.x;
+    if (w < S.whole) {
+      tile = xcd_remap(w, S.whole);
+      ke = S.nk;
+      one = true;
+      return;
+    }
+    const int64_t u = xcd_remap(w - S.whole, gridDim.x - S.whole);
+    const int64_t sliced = S.ragged * S.full;
+    if (u < sliced) {
+      part = static_cast<int>(u / S.ragged);
+      tile = S.whole + (u - part * S.ragged);
+      kb = part * S.ipw;
+      ke = kb + S.ipw;
+      one = true;
+    } else {
+      remainder = true;
+      it = (u - sliced) * S.ipw;
+      it_end = min(S.ragged * S.rem, it + S.ipw);
+    }
+  }
+  __device__ __forceinline__ bool next(const SSched& S) {
+    if (!remainder) {
+      const bool r = one;
+      one = false;
+      return r;
+    }
+    if (it >= it_end) return false;
+    const int64_t rt = it / S.rem;
+    const int r0 = static_cast<int>(it - rt * S.rem);
+    const int r1 = static_cast<int>(min<int64_t>(S.rem, r0 + (it_end - it)));
+    tile = S.whole + rt;
+    kb = S.full * S.ipw + r0;
+    ke = S.full * S.ipw + r1;
+    part = S.full + static_cast<int>(it / S.ipw - (rt * S.rem) / S.ipw);
+    it += r1 - r0;
+    return true;
+  }
+};
 
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
+struct TilePos {
+  int64_t grp, m0, mlim, n0;
+  bool second;   // in the second row segment of A
+};
+template <int BM, int BN>
+__device__ __forceinline__ TilePos tile_pos(const SSched& S, int64_t M, int64_t msplit, int64_t tile) {
+  TilePos p;
+  p.grp = tile / S.tpg;
+  int tm, tn;
+  tile_coords_banded(tile - p.grp * S.tpg, S.tiles_m, S.tiles_n, tm, tn);
+  p.second = tm >= S.tm0;
+  p.m0 = p.second ? msplit + static_cast<int64_t>(tm - S.tm0) * BM : static_cast<int64_t>(tm) * BM;
+  p.mlim = p.second ? M : msplit;
+  p.n0 = static_cast<int64_t>(tn) * BN;
+  return p;
+}
+
+template <int WM, int WN>
+__device__ __forceinline__ bool any_nonfinite(const floatx16 (&acc)[WM][WN]) {
+  float z = 0.f;
+#pragma unroll
+  for (int a = 0; a < WM; ++a)
+#pragma unroll
+    for (int b = 0; b < WN; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) z = fmaf(acc[a][b][r], 0.f, z);
+  return __any(!(z == 0.f));
+}
+
+// This wave's block (rows wr.., columns wc.. of the tile, rows_left and
+// cols_left in the tile) over K steps [kb, ke) on the fp32 matrix
+// instruction, from memory.
+template <int WM, int WN, int KW, bool AK, bool BK>
+__device__ __forceinline__ void recompute(floatx16 (&acc)[WM][WN], const SSched& S, int64_t K, int64_t ksplit,
+                                          int kb, int ke, const float* a0, const float* a1, int64_t lda,
+                                          const float* b0, int64_t ldb, int wr, int wc, int64_t rows_left,
+                                          int64_t cols_left) {
+  const int li = threadIdx.x & 31, lh = (threadIdx.x >> 5) & 1;
+#pragma unroll
+  for (int a = 0; a < WM; ++a)
+#pragma unroll
+    for (int b = 0; b < WN; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+  for (int j = kb; j < ke; ++j) {
+    int64_t k0;
+    int klim;
+    bool second;
+    k_step<KW>(S, K, ksplit, j, k0, klim, second);
+    const float* pa = AK ? (second ? a1 + (k0 - ksplit) : a0 + k0) : a0 + k0 * lda;
+    const float* pb = BK ? b0 + k0 : b0 + k0 * ldb;
+    for (int kk = 0; kk < klim; kk += 2) {
+      const int k = min(kk + lh, klim - 1);
+      const bool in = kk + lh < klim;
+      float x[WM], y[WN];
+#pragma unroll
+      for (int a = 0; a < WM; ++a) {
+        const int64_t r = min<int64_t>(wr + a * 32 + li, rows_left - 1);
+        const float e = AK ? pa[r * lda + k] : pa[k * lda + r];
+        x[a] = in ? e : 0.f;
+      }
+#pragma unroll
+      for (int b = 0; b < WN; ++b) {
+        const int64_t r = min<int64_t>(wc + b * 32 + li, cols_left - 1);
+        const float e = BK ? pb[r * ldb + k] : pb[k * ldb + r];
+        y[b] = in ? e : 0.f;
+      }
+#pragma unroll
+      for (int a = 0; a < WM; ++a)
+#pragma unroll
+        for (int b = 0; b < WN; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[a], y[b], acc[a][b], 0, 0, 0);
+    }
+  }
+}
+
+// One 32 x 32 block to C.  Accumulator register r of lane l: row
+// 8 (r / 4) + 4 (l / 32) + (r mod 4), column l mod 32.  The mask and the
+// weights of a fused SGD step are all read before anything is written.
+// WHOLE: all 32 rows lie in the matrix.
+template <bool WHOLE>
+__device__ __forceinline__ void store_block(const floatx16& acc, const SOut& C, int64_t row0, int64_t mlim,
+                                            int64_t col, int64_t N) {
+  if (col >= N) return;
+  const bool lo = col < C.c_split;
+  const int64_t ld = lo ? C.ldc0 : C.ldc1;
+  float* p = lo ? C.c0 + row0 * C.ldc0 + col : C.c1 + row0 * C.ldc1 + (col - C.c_split);
+  const int left = static_cast<int>(min<int64_t>(mlim - row0, 32));
+  float v[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) v[r] = C.relu ? fmaxf(acc[r], 0.f) : acc[r];
+  if (C.mask && lo) {
+    const float* m = C.mask + row0 * C.ldm + col;
+    float k[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int rr = 8 * (r >> 2) + (r & 3);
+      k[r] = WHOLE || rr < left ? m[rr * C.ldm] : 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = k[r] > 0.f ? v[r] : 0.f;
+  }
+  if (C.sgd) {
+    float w[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int rr = 8 * (r >> 2) + (r & 3);
+      w[r] = WHOLE || rr < left ? p[rr * ld] : 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = fmaf(-C.lr, v[r], w[r]);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int rr = 8 * (r >> 2) + (r & 3);
+    if (WHOLE || rr < left) p[rr * ld] = v[r];
+  }
+}
+
+// This wave's block of a tile whose whole K it holds.
+template <int WM, int WN>
+__device__ __forceinline__ void store_tile(const floatx16 (&acc)[WM][WN], const SOut& C, int64_t grp, int64_t row,
+                                           int64_t mlim, int64_t col, int64_t N) {
+  const int li = threadIdx.x & 31, lh = (threadIdx.x >> 5) & 1;
+  SOut Cg = C;
+  Cg.c0 += grp * C.gs0;
+  Cg.c1 += grp * C.gs1;
+  if (C.mask) Cg.mask += grp * C.gsm;
+#pragma unroll
+  for (int a = 0; a < WM; ++a)
+#pragma unroll
+    for (int b = 0; b < WN; ++b) {
+      const int64_t r0 = row + a * 32 + 4 * lh, c = col + b * 32 + li;
+      if (row + a * 32 + 32 <= mlim) store_block<true>(acc[a][b], Cg, r0, mlim, c, N);
+      else store_block<false>(acc[a][b], Cg, r0, mlim, c, N);
+    }
+}
+
+// A partial tile in accumulator order (block, r / 4, lane, r mod 4): 16-byte
+// stores of whole lines.
+template <int WM, int WN>
+__device__ __forceinline__ void store_part(const floatx16 (&acc)[WM][WN], float sg, float* part, int wave) {
+  floatx4* dst = reinterpret_cast<floatx4*>(part) + wave * (WM * WN * 256) + (threadIdx.x & 63);
+#pragma unroll
+  for (int a = 0; a < WM; ++a)
+#pragma unroll
+    for (int b = 0; b < WN; ++b)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        floatx4 x;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = sg * acc[a][b][4 * r4 + q];
+        dst[((a * WN + b) * 4 + r4) * 64] = x;
+      }
+}
+
+// The fp32 product.  NWM x NWN waves of 32 WM x 32 WN blocks; 256 x 256 tiles
+// by eight waves (one workgroup per CU) or 128 x 128 by four (two).  Every
+// K step of 16 is 6 WM WN MFMAs per wave between two barriers; three LDS
+// buffers of 6 bytes per value (144 KB at 256 x 256).  Larger tiles halve the
+// splitting work and LDS traffic per MFMA (95 VALU to 48 MFMAs per wave and
+// step at 256 x 256, twice that at 128 x 128), which is what is left of
+// the power for the matrix cores.
+template <int WM, int WN, int NWM, int NWN, bool AK, bool BK, int V>
+__global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
+    int64_t M, int64_t N, int64_t K, int64_t msplit, int64_t ksplit, SOp A, SOp B, SOut C, SSched S,
+    float* __restrict__ partials) {
+  constexpr int THR = 64 * NWM * NWN;
+  constexpr int BM = 32 * WM * NWM, BN = 32 * WN * NWN;
+  constexpr int ABYTES = 3 * plane_bytes<BM>(), BBYTES = 3 * plane_bytes<BN>();
+  __shared__ __attribute__((aligned(16))) char lds[3][ABYTES + BBYTES];
+  using SA = Stage<3, AK, V, BM, THR, KS, unsigned>;
+  using SB = Stage<3, BK, V, BN, THR, KS, unsigned>;
+
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int li = lane & 31, lh = lane >> 5;
-  constexpr int NC = NARROW ? 2 : BK / 8;   // 8-wide K chunks per wave per fp32 step
-  const int cb = NARROW ? 2 * wn : 0;       // this wave's first chunk
-  const int bw = NARROW ? 0 : wn;           // this wave's 64-column block of the tile
+  const int wm = wave / NWN, wn = wave % NWN;
+  const int frag = lh * 512 + lds_slot(li, lh) * 16;   // this lane's chunk in a 32-row block
 
-  // K per pipeline step: one 32-wide load sub-tile for fp32, two for bf16
-  constexpr int KS = BF16 ? KSH : BK;
-  constexpr int SUB = KS / BK;
-  floatx16 acc[2][2];
-  floatx4 ra[SUB][4], rb[SUB][4];
-  int64_t m0 = 0, n0 = 0;
-  OpDev Ag = A, Bg = B;   // this tile's group of A, B and C
-  OutDev Cg = C;
-
-  auto stage = [&](int buf) {
-    if constexpr (BF16) {
-#pragma unroll
-      for (int s = 0; s < SUB; ++s) {
-        store_tile_bf16<AK, AV>(lds_h + buf * kStageH, ra[s], s * BK);
-        store_tile_bf16<BK_, BV>(lds_h + buf * kStageH + BM * LDKH, rb[s], s * BK);
-      }
+  Units units(S);
+  // Where the registers allow it the five small products have accumulators
+  // of their own, added at the end: the large sums then round twice per step
+  // (each instruction adds its two halves of K in turn), not twelve times.
+  constexpr bool DUAL = WM * WN <= 4;
+  // (Error of a product over K = 1,433: 9.3e-8 against 1.8e-7 with one set, and
+  // 3.1e-7 on the fp32 instruction.)
+  floatx16 acc[WM][WN], low[DUAL ? WM : 1][DUAL ? WN : 1];
+  SA sa;
+  SB sb;
+  while (units.next(S)) {
+    const int kb = units.kb, ke = units.ke;
+    const TilePos tp = tile_pos<BM, BN>(S, M, msplit, units.tile);
+    const int64_t m0 = tp.m0, mlim = tp.mlim, n0 = tp.n0, grp = tp.grp;
+    // first element of the tile's first row / column, per K segment
+    const float *a0, *a1;
+    if constexpr (AK) {
+      a0 = A.p0 + grp * A.gs0 + m0 * A.ld;
+      a1 = A.p1 + grp * A.gs1 + m0 * A.ld;
     } else {
-      store_tile_f32<AK, AV>(lds_f + buf * kStage, ra[0]);
-      store_tile_f32<BK_, BV>(lds_f + buf * kStage + kTileF, rb[0]);
+      a0 = a1 = tp.second ? A.p1 + grp * A.gs1 + (m0 - msplit) : A.p0 + grp * A.gs0 + m0;
     }
-  };
-  auto load_full = [&](int64_t k) {
+    const float* b0 = B.p0 + grp * B.gs0 + (BK ? n0 * B.ld : n0);
+    const unsigned lda4 = static_cast<unsigned>(A.ld * 4), ldb4 = static_cast<unsigned>(B.ld * 4);
+    sa.init(A.ld, static_cast<int>(min<int64_t>(BM, mlim - m0)), t);
+    sb.init(B.ld, static_cast<int>(min<int64_t>(BN, N - n0)), t);
+    constexpr int NIT = SA::NI + SB::NI;   // load items per thread, A's first
+    // The bf16 unit's sums round a little toward minus infinity (0.003 of a
+    // unit in the last place per instruction, on average), which would add up
+    // over a long K: a workgroup takes at most 4,096 values of K, and
+    // the parts of a tile take turns at accumulating the product and its
+    // negative (A negated on its way to LDS), so that the bias cancels.
+    float sg = units.part & 1 ? -1.f : 1.f;
+    struct Src { const char *a, *b; int klim; };
+    auto src_full = [&](int j) {           // where whole step j is
+      const bool second = j >= S.nf0;
+      const int64_t k0 = static_cast<int64_t>(second ? j - S.nf0 : j) * KS + (second ? ksplit : 0);
+      return Src{reinterpret_cast<const char*>(AK ? (second ? a1 + (k0 - ksplit) : a0 + k0) : a0 + k0 * A.ld),
+                 reinterpret_cast<const char*>(BK ? b0 + k0 : b0 + k0 * B.ld), KS};
+    };
+    auto src_any = [&](int j) {
+      int64_t k0;
+      int klim;
+      bool second;
+      k_step<KS>(S, K, ksplit, j, k0, klim, second);
+      return Src{reinterpret_cast<const char*>(AK ? (second ? a1 + (k0 - ksplit) : a0 + k0) : a0 + k0 * A.ld),
+                 reinterpret_cast<const char*>(BK ? b0 + k0 : b0 + k0 * B.ld), klim};
+    };
+    auto load = [&](auto edge, int i, const Src& q) {
+      constexpr bool E = decltype(edge)::value;
+      if (i < SA::NI) sa.template load<E>(i, q.a, lda4, q.klim, t);
+      else sb.template load<E>(i - SA::NI, q.b, ldb4, q.klim, t);
+    };
+    // split item i (its groups) into LDS buffer buf
+    auto stage = [&](auto edge, int buf, int i, int klim) {
+      constexpr bool E = decltype(edge)::value;
+      if (i < SA::NI) {
 #pragma unroll
-    for (int s = 0; s < SUB; ++s) {
-      load_tile<AK, AV, true>(Ag, M, K, m0, k + s * BK, ra[s]);
-      load_tile<BK_, BV, true>(Bg, N, K, n0, k + s * BK, rb[s]);
-    }
-  };
-  auto load_edge = [&](int64_t k) {
-#pragma unroll
-    for (int s = 0; s < SUB; ++s) {
-      load_tile<AK, AV, false>(Ag, M, K, m0, k + s * BK, ra[s]);
-      load_tile<BK_, BV, false>(Bg, N, K, n0, k + s * BK, rb[s]);
-    }
-  };
-  auto compute = [&](int buf) {
-    if constexpr (BF16) {
-      const unsigned short* As = lds_h + buf * kStageH;
-      const unsigned short* Bs = As + BM * LDKH;
-      // K chunks of 16; lane half h supplies K values 8h .. 8h+7
-#pragma unroll
-      for (int c = 0; c < KS / 16; ++c) {
-        bf16x8 av[2], bv[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          av[t] = *reinterpret_cast<const bf16x8*>(As + (wm * 64 + t * 32 + li) * LDKH + 16 * c + 8 * lh);
-          bv[t] = *reinterpret_cast<const bf16x8*>(Bs + (wn * 64 + t * 32 + li) * LDKH + 16 * c + 8 * lh);
-        }
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 2; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[a], bv[b], acc[a][b], 0, 0, 0);
-      }
-    } else {
-      const float* As = lds_f + buf * kStage;
-      const float* Bs = As + kTileF;
-      if constexpr (kPipeFrag<AK, BK_, AV, BV>()) {
-        // fragments of chunk c+1 are read while chunk c multiplies
-        floatx4 av[2][2], bv[2][2];
-        auto rd = [&](int c, int p) {
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            av[p][t] = frag_f32(As, wm * 64 + t * 32 + li, 8 * c + 4 * lh);
-            bv[p][t] = frag_f32(Bs, bw * 64 + t * 32 + li, 8 * c + 4 * lh);
-          }
-        };
-        rd(cb, 0);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          if (c + 1 < NC) rd(cb + c + 1, (c + 1) & 1);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-              for (int b = 0; b < 2; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[c & 1][a][s], bv[c & 1][b][s],
-                                                                 acc[a][b], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int g = 0; g < SA::GP; ++g) sa.template store<E, true>(lds[buf], i * SA::GP + g, klim, sg, t);
       } else {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          floatx4 av[2], bv[2];
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            av[t] = frag_f32(As, wm * 64 + t * 32 + li, 8 * (cb + c) + 4 * lh);
-            bv[t] = frag_f32(Bs, bw * 64 + t * 32 + li, 8 * (cb + c) + 4 * lh);
-          }
-#pragma unroll
-          for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-              for (int b = 0; b < 2; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[a][s], bv[b][s], acc[a][b], 0, 0, 0);
-          // one K chunk's fragments live at a time (keeps two waves per SIMD)
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-  };
-
-  // fp32 step j with step j+1's staging (its registers to LDS buffer nbuf,
-  // free since the barrier that ended step j-1) placed among the MFMAs of
-  // chunk 2: the transposes and LDS writes issue while the matrix core runs,
-  // instead of after the last MFMA, when the other wave of the SIMD may be
-  // staging too.  Same arithmetic, same order as compute then stage.
-  auto compute_staged = [&](int buf, int nbuf) {
-    const float* As = lds_f + buf * kStage;
-    const float* Bs = As + kTileF;
-    auto mfma16 = [&](const floatx4 (&av)[2], const floatx4 (&bv)[2]) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 2; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[a][q], bv[b][q], acc[a][b], 0, 0, 0);
-    };
-    auto interleave = [&]() {
-#pragma unroll
-      for (int g = 0; g < 8; ++g) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);   // up to four VALU
-        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);   // an LDS write
+        for (int g = 0; g < SB::GP; ++g)
+          sb.template store<E, false>(lds[buf] + ABYTES, (i - SA::NI) * SB::GP + g, klim, sg, t);
       }
     };
-    if constexpr (kPipeFrag<AK, BK_, AV, BV>()) {
-      floatx4 av[2][2], bv[2][2];
-      auto rd = [&](int c, int p) {
+    constexpr std::true_type kEdge{};
+    constexpr std::false_type kFull{};
+    bf16x8 av[WM][3], bv[2][3];
+    auto read_a = [&](int buf, int a, int p) {
+      av[a][p] = *reinterpret_cast<const bf16x8*>(lds[buf] + (wm * WM + a) * 1024 + frag +
+                                                  p * plane_bytes<BM>());
+    };
+    auto read_b = [&](int buf, int b, int p) {
+      bv[b & 1][p] = *reinterpret_cast<const bf16x8*>(lds[buf] + ABYTES + (wn * WN + (b % WN)) * 1024 +
+                                                      frag + p * plane_bytes<BN>());
+    };
+    // The six products of block column b, smallest first; plane p of A is
+    // last used at kLastA[p], so its registers can take the next step's.
+    constexpr int TA[6] = {2, 1, 1, 0, 0, 0}, TB[6] = {0, 1, 0, 2, 1, 0};
+    auto mfmas = [&](int b, int q) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          av[p][t] = frag_f32(As, wm * 64 + t * 32 + li, 8 * c + 4 * lh);
-          bv[p][t] = frag_f32(Bs, bw * 64 + t * 32 + li, 8 * c + 4 * lh);
-        }
-      };
-      rd(cb, 0);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if (c + 1 < NC) rd(cb + c + 1, (c + 1) & 1);
-        __builtin_amdgcn_sched_barrier(0);
-        if (c == 1) stage(nbuf);
-        mfma16(av[c & 1], bv[c & 1]);
-        if (c == 1) interleave();
-        __builtin_amdgcn_sched_barrier(0);
+      for (int a = 0; a < WM; ++a) {
+        floatx16& c = DUAL && q < 5 ? low[DUAL ? a : 0][DUAL ? b : 0] : acc[a][b];
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[a][TA[q]], bv[b & 1][TB[q]], c, 0, 0, 0);
       }
-    } else {
+    };
+    // One K step from LDS buffer cur.  Every block of MFMAs also splits some
+    // of step j + 2's items (in registers) into buffer free and at once
+    // reloads them with step j + 3, so that a load has a whole step to
+    // arrive; the last block reads the fragments that step j + 1 (in buffer
+    // next, complete since the last barrier) starts with, so that its MFMAs
+    // follow the barrier at once.
+    auto step = [&](int cur, int next, int free, int jload) {
+      const Src src = src_full(jload);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        floatx4 av[2], bv[2];
+      for (int a = 0; a < WM; ++a) read_a(cur, a, 0);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          av[t] = frag_f32(As, wm * 64 + t * 32 + li, 8 * (cb + c) + 4 * lh);
-          bv[t] = frag_f32(Bs, bw * 64 + t * 32 + li, 8 * (cb + c) + 4 * lh);
+      for (int b = 0; b < WN; ++b) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) read_b(b + 1 < WN ? cur : next, b + 1, p);
+#pragma unroll
+        for (int i = b * NIT / WN; i < (b + 1) * NIT / WN; ++i) {
+          stage(kFull, free, i, KS);
+          load(kFull, i, src);
         }
-        if (c == 1) stage(nbuf);
-        mfma16(av, bv);
-        if (c == 1) interleave();
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  };
-
-  const int64_t w = xcd_remap(blockIdx.x, gridDim.x);
-  int64_t it, it_end;
-  if (S.spu > 0) {
-    // K-slice-major: workgroup w takes K slice w / tiles of tile w % tiles,
-    // so the workgroups an XCD runs together (consecutive w) cover every
-    // tile of the same K range and share its operand rows in L2
-    const int64_t q = w / S.tiles, t = w - q * S.tiles;
-    const int64_t kb = q * S.spu;
-    it = t * S.nk + kb;
-    it_end = t * S.nk + min<int64_t>(S.nk, kb + S.spu);
-  } else {
-    it = w * S.ipw;
-    it_end = min(S.T, it + S.ipw);
-  }
-  const int64_t first_tile = it / S.nk;
-  const bool k_ragged = K % KS != 0;
-
-  while (it < it_end) {
-    const int64_t tile = it / S.nk;
-    const int kb = static_cast<int>(it % S.nk);
-    const int ke = static_cast<int>(min<int64_t>(S.nk, kb + (it_end - it)));
-    const int64_t grp = tile / S.tpg;
-    int tm, tn;
-    tile_coords_banded(tile - grp * S.tpg, S.tiles_m, S.tiles_n, tm, tn);
-    m0 = static_cast<int64_t>(tm) * BM;
-    n0 = static_cast<int64_t>(tn) * BN;
-    Ag = A.group(grp);
-    Bg = B.group(grp);
-    Cg = C.group(grp);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+        for (int q = 0; q < 6; ++q) {
+          mfmas(b, q);
+          if (b == WN - 1 && q == 0) {
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-
-    // K steps [kb, ke) of this tile; the tile's last step may be partial
-    const bool tail = ke == S.nk && k_ragged;
-    const int full_end = tail ? ke - 1 : ke;
-    __syncthreads();  // LDS of the previous segment fully consumed
-    if (kb < full_end) {
-      load_full(static_cast<int64_t>(kb) * KS);
-      stage(0);
-      __syncthreads();
-      // steady state: prefetch step j+1 into registers while step j computes
-      for (int j = kb; j + 1 < full_end; ++j) {
-        load_full(static_cast<int64_t>(j + 1) * KS);
-        // keep the prefetch at the top of the iteration: without the fence
-        // the scheduler sinks the loads next to their LDS stores, and their
-        // latency is no longer hidden behind the step's MFMAs
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (BF16) {
-          compute((j - kb) & 1);
-          __builtin_amdgcn_sched_barrier(0);
-          stage((j + 1 - kb) & 1);
-        } else {
-          compute_staged((j - kb) & 1, (j + 1 - kb) & 1);
-        }
-        __syncthreads();
-      }
-      compute((full_end - 1 - kb) & 1);
-    }
-    if (tail) {
-      const int buf = (full_end - kb) & 1;
-      load_edge(static_cast<int64_t>(full_end) * KS);
-      __syncthreads();
-      stage(buf);
-      __syncthreads();
-      compute(buf);
-    }
-
-    if constexpr (NARROW) {
-      // each wave adds its partner's K half (waves 2i and 2i+1 hold the two
-      // halves of the same 64 x 64 block; a + b == b + a, so both end with
-      // the same sums), without a branch on the wave
-      __syncthreads();   // every wave is done reading this segment's tiles
-      float* mine = lds_f + wave * 4096;
-      const float* other = lds_f + (wave ^ 1) * 4096;
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) mine[((a * 2 + b) * 16 + r) * 64 + lane] = acc[a][b][r];
-      __syncthreads();
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[a][b][r] += other[((a * 2 + b) * 16 + r) * 64 + lane];
-          __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-
-    // Epilogue.  Accumulator register r of lane l holds C row
-    // 8 (r / 4) + 4 (l / 32) + (r mod 4), column l mod 32 of its 32 x 32 tile.
-    // (NARROW: the waves of column block 1 hold columns 64.. >= N and store
-    // nothing.)
-    if (kb == 0 && ke == S.nk) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const int64_t col = n0 + wn * 64 + b * 32 + li;
-          if (col >= N) continue;
-          if (Cg.sgd) {
-            // fused SGD step: the sub-tile's 16 weights are read before any is
-            // written (one memory latency, not sixteen; reading the next
-            // sub-tile's ahead would need registers these kernels lack)
-            float w[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int64_t row = m0 + wm * 64 + a * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-              w[r] = row < M ? *out_ptr(Cg, row, col) : 0.f;
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int64_t row = m0 + wm * 64 + a * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-              if (row < M) *out_ptr(Cg, row, col) = fmaf(-Cg.lr, acc[a][b][r], w[r]);
-            }
-            continue;
+            for (int a = 0; a < WM; ++a) read_a(next, a, 2);
           }
+          if (b == WN - 1 && q == 2) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int64_t row = m0 + wm * 64 + a * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-            if (row < M) store_out(Cg, row, col, acc[a][b][r]);
+            for (int a = 0; a < WM; ++a) read_a(next, a, 1);
           }
         }
-    } else if (!NARROW || wn == 0) {
-      // partial tile: slot 0 holds this workgroup's first tile, slot 1 its last
-      float* part = partials + (w * 2 + (tile == first_tile ? 0 : 1)) * (BM * BN);
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+        for (int q = 0; q < 6 * WM; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // an MFMA
+          __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);   // some VALU
+          __builtin_amdgcn_sched_group_barrier(0x080, 1, 0);   // an LDS access
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+    for (int a = 0; a < WM; ++a)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int rr = wm * 64 + a * 32 + 8 * (r >> 2) + 4 * lh + (r & 3);
-            const int cc = wn * 64 + b * 32 + li;
-            part[rr * BN + cc] = acc[a][b][r];
+      for (int b = 0; b < WN; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          acc[a][b][r] = 0.f;
+          if (DUAL) low[DUAL ? a : 0][DUAL ? b : 0][r] = 0.f;
+        }
+
+    // a wave wholly past the matrix only stages
+    const bool live = wm * WM * 32 < mlim - m0 && wn * WN * 32 < N - n0;
+    lds_barrier();   // the previous tile's LDS is consumed
+    const int fe = min(ke, S.nf);
+    if (kb < fe) {
+      {
+        Src q = src_full(kb);
+#pragma unroll
+        for (int i = 0; i < NIT; ++i) load(kFull, i, q);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          q = src_full(min(kb + s + 1, fe - 1));
+#pragma unroll
+          for (int i = 0; i < NIT; ++i) {
+            stage(kFull, s, i, KS);
+            load(kFull, i, q);
           }
+        }
+      }
+      lds_barrier();
+      int cur = 0, next = 1, free = 2;
+      if (live) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          read_b(0, 0, p);
+#pragma unroll
+          for (int a = 0; a < WM; ++a) read_a(0, a, p);
+        }
+        for (int j = kb; j < fe; ++j) {
+          step(cur, next, free, min(j + 3, fe - 1));
+          lds_barrier();
+          const int c = cur;
+          cur = next;
+          next = free;
+          free = c;
+        }
+      } else {
+        for (int j = kb; j < fe; ++j) {
+          const Src q = src_full(min(j + 3, fe - 1));
+#pragma unroll
+          for (int i = 0; i < NIT; ++i) {
+            stage(kFull, free, i, KS);
+            load(kFull, i, q);
+          }
+          lds_barrier();
+          const int c = cur;
+          cur = next;
+          next = free;
+          free = c;
+        }
+      }
     }
-    it += ke - kb;
+    for (int j = max(kb, S.nf); j < ke; ++j) {   // the segments' partial steps
+      const Src q = src_any(j);
+#pragma unroll
+      for (int i = 0; i < NIT; ++i) load(kEdge, i, q);
+#pragma unroll
+      for (int i = 0; i < NIT; ++i) stage(kEdge, 0, i, q.klim);
+      lds_barrier();
+      if (live) {
+#pragma unroll
+        for (int a = 0; a < WM; ++a)
+#pragma unroll
+          for (int p = 0; p < 3; ++p) read_a(0, a, p);
+#pragma unroll
+        for (int b = 0; b < WN; ++b) {
+#pragma unroll
+          for (int p = 0; p < 3; ++p) read_b(0, b, p);
+#pragma unroll
+          for (int q6 = 0; q6 < 6; ++q6) mfmas(b, q6);
+        }
+      }
+      lds_barrier();
+    }
+
+    if constexpr (DUAL) {
+#pragma unroll
+      for (int a = 0; a < WM; ++a)
+#pragma unroll
+        for (int b = 0; b < WN; ++b) acc[a][b] += low[a][b];
+    }
+    if (any_nonfinite<WM, WN>(acc)) {
+      sg = 1.f;
+      recompute<WM, WN, KS, AK, BK>(acc, S, K, ksplit, kb, ke, a0, a1, A.ld, b0, B.ld, wm * WM * 32,
+                                    wn * WN * 32, mlim - m0, N - n0);
+    }
+    if (kb == 0 && ke == S.nk)
+      store_tile<WM, WN>(acc, C, grp, m0 + wm * WM * 32, mlim, n0 + wn * WN * 32, N);
+    else
+      store_part<WM, WN>(acc, sg,
+                         partials + ((units.tile - S.whole) * S.parts + units.part) * static_cast<int64_t>(BM * BN),
+                         wave);
   }
 }
 
-// Sum the partial tiles of every tile split between workgroups, in
-// workgroup order, and apply the epilogue.  Grid: (tile, 8-row chunk of the
-// tile), so that a tile split over many workgroups (a thin dW = H^T dZ with
-// a long K) is still summed by 16 blocks; each thread sums one float4 of
-// every partial, in workgroup order (bitwise the same for any grid shape).
-constexpr int kMaxFixupParts = 1024;
-constexpr int kFixRows = 8;
-constexpr int kFixChunks = BM / kFixRows;
-static_assert(kFixRows * BN == 4 * 256, "one float4 per thread per partial");
-
-__global__ __launch_bounds__(256) void streamk_fixup(int64_t M, int64_t N, Sched S,
-                                                     const float* __restrict__ partials,
-                                                     OutDev C) {
-  __shared__ int64_t slot_off[kMaxFixupParts];
-  const int64_t t = blockIdx.x;
-  const int chunk = blockIdx.y;
-  const bool sliced = S.spu > 0;
-  const int64_t w_first = sliced ? 0 : (t * S.nk) / S.ipw;
-  const int64_t w_last = sliced ? (S.nk + S.spu - 1) / S.spu - 1 : ((t + 1) * S.nk - 1) / S.ipw;
-  if (w_first == w_last) return;  // computed whole and stored by one workgroup
-  const int64_t grp = t / S.tpg;
-  int tm, tn;
-  tile_coords_banded(t - grp * S.tpg, S.tiles_m, S.tiles_n, tm, tn);
-  const int64_t m0 = static_cast<int64_t>(tm) * BM, n0 = static_cast<int64_t>(tn) * BN;
-  if (m0 + chunk * kFixRows >= M) return;   // the chunk lies below the matrix
-  const int parts = static_cast<int>(w_last - w_first + 1);
-  for (int j = threadIdx.x; j < parts; j += 256) {
-    // sliced: slice j of tile t is workgroup j * tiles + t, its only tile
-    const int64_t w = w_first + j;
-    slot_off[j] = sliced ? (j * S.tiles + t) * 2 * (BM * BN)
-                         : (w * 2 + (((w * S.ipw) / S.nk) == t ? 0 : 1)) * (BM * BN);
+// Small products, and products with bf16 inputs (NP = 1: operands rounded to
+// bf16, one product): four waves of 32 WM x 32 WN blocks, K steps of 64 so
+// that a workgroup meets the memory latency once per 64 values of K.  One LDS
+// tile (three workgroups per CU), the next step's loads in flight while this
+// one multiplies.
+constexpr int KL = 64;
+template <int NP, int WM, int WN, bool AK, bool BK, int V>
+__global__ __launch_bounds__(256, WM == 1 ? 3 : 2) void gemm_small_kernel(
+    int64_t M, int64_t N, int64_t K, int64_t msplit, int64_t ksplit, SOp A, SOp B, SOut C, SSched S,
+    float* __restrict__ partials) {
+  constexpr int BM = 64 * WM, BN = 64 * WN;
+  constexpr int CA = NP * plane_bytes<BM>(), CB = NP * plane_bytes<BN>();   // bytes of 16 K
+  __shared__ __attribute__((aligned(16))) char lds[(KL / 16) * (CA + CB)];
+  using SA = Stage<NP, AK, V, BM, 256, KL, int64_t>;
+  using SB = Stage<NP, BK, V, BN, 256, KL, int64_t>;
+  constexpr bool EXACT = NP == 3;
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int frag = (lane >> 5) * 512 + lds_slot(lane & 31, lane >> 5) * 16;
+  char* const ldsB = lds + (KL / 16) * CA;
+  floatx16 acc[WM][WN], low[EXACT ? WM : 1][EXACT ? WN : 1];   // low: the five small products
+  SA sa;
+  SB sb;
+  Units units(S);
+  while (units.next(S)) {
+    const int kb = units.kb, ke = units.ke;
+    const TilePos tp = tile_pos<BM, BN>(S, M, msplit, units.tile);
+    const int64_t m0 = tp.m0, n0 = tp.n0, grp = tp.grp;
+    const float *a0, *a1;
+    if constexpr (AK) {
+      a0 = A.p0 + grp * A.gs0 + m0 * A.ld;
+      a1 = A.p1 + grp * A.gs1 + m0 * A.ld;
+    } else {
+      a0 = a1 = tp.second ? A.p1 + grp * A.gs1 + (m0 - msplit) : A.p0 + grp * A.gs0 + m0;
+    }
+    const float* b0 = B.p0 + grp * B.gs0 + (BK ? n0 * B.ld : n0);
+    sa.init(A.ld, static_cast<int>(min<int64_t>(BM, tp.mlim - m0)), t);
+    sb.init(B.ld, static_cast<int>(min<int64_t>(BN, N - n0)), t);
+    auto load = [&](int j) {
+      int64_t k0;
+      int klim;
+      bool second;
+      k_step<KL>(S, K, ksplit, j, k0, klim, second);
+      const char* pa = reinterpret_cast<const char*>(
+          AK ? (second ? a1 + (k0 - ksplit) : a0 + k0) : a0 + k0 * A.ld);
+      const char* pb = reinterpret_cast<const char*>(BK ? b0 + k0 : b0 + k0 * B.ld);
+#pragma unroll
+      for (int i = 0; i < SA::NI; ++i) sa.template load<true>(i, pa, A.ld * 4, klim, t);
+#pragma unroll
+      for (int i = 0; i < SB::NI; ++i) sb.template load<true>(i, pb, B.ld * 4, klim, t);
+      return klim;
+    };
+    float sg = EXACT && (units.part & 1) ? -1.f : 1.f;   // see gemm_split_kernel
+#pragma unroll
+    for (int a = 0; a < WM; ++a)
+#pragma unroll
+      for (int b = 0; b < WN; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          acc[a][b][r] = 0.f;
+          if (EXACT) low[EXACT ? a : 0][EXACT ? b : 0][r] = 0.f;
+        }
+    int klim = load(kb);
+    for (int j = kb; j < ke; ++j) {
+      lds_barrier();   // the last step's fragments are read
+#pragma unroll
+      for (int g = 0; g < SA::NG; ++g) sa.template store<true, EXACT>(lds, g, klim, sg, t);
+#pragma unroll
+      for (int g = 0; g < SB::NG; ++g) sb.template store<true, false>(ldsB, g, klim, sg, t);
+      if (j + 1 < ke) klim = load(j + 1);
+      lds_barrier();
+#pragma unroll
+      for (int c = 0; c < KL / 16; ++c) {
+        bf16x8 av[WM][NP], bv[WN][NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+#pragma unroll
+          for (int a = 0; a < WM; ++a)
+            av[a][p] = *reinterpret_cast<const bf16x8*>(lds + c * CA + p * plane_bytes<BM>() +
+                                                        (wm * WM + a) * 1024 + frag);
+#pragma unroll
+          for (int b = 0; b < WN; ++b)
+            bv[b][p] = *reinterpret_cast<const bf16x8*>(ldsB + c * CB + p * plane_bytes<BN>() +
+                                                        (wn * WN + b) * 1024 + frag);
+        }
+#pragma unroll
+        for (int a = 0; a < WM; ++a)
+#pragma unroll
+          for (int b = 0; b < WN; ++b) {
+            if constexpr (EXACT) {
+              constexpr int TA[5] = {2, 1, 0, 1, 0}, TB[5] = {0, 1, 2, 0, 1};
+#pragma unroll
+              for (int q = 0; q < 5; ++q)
+                low[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[a][TA[q]], bv[b][TB[q]], low[a][b], 0, 0, 0);
+            }
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[a][0], bv[b][0], acc[a][b], 0, 0, 0);
+          }
+      }
+    }
+    if constexpr (EXACT) {
+#pragma unroll
+      for (int a = 0; a < WM; ++a)
+#pragma unroll
+        for (int b = 0; b < WN; ++b) acc[a][b] += low[a][b];
+      if (any_nonfinite<WM, WN>(acc)) {
+        sg = 1.f;
+        recompute<WM, WN, KL, AK, BK>(acc, S, K, ksplit, kb, ke, a0, a1, A.ld, b0, B.ld, wm * WM * 32,
+                                      wn * WN * 32, tp.mlim - m0, N - n0);
+      }
+    }
+    if (kb == 0 && ke == S.nk)
+      store_tile<WM, WN>(acc, C, grp, m0 + wm * WM * 32, tp.mlim, n0 + wn * WN * 32, N);
+    else
+      store_part<WM, WN>(acc, sg,
+                         partials + ((units.tile - S.whole) * S.parts + units.part) * static_cast<int64_t>(BM * BN),
+                         wave);
   }
-  __syncthreads();
-  const OutDev Cg = C.group(grp);
-  const int e = chunk * kFixRows * BN + threadIdx.x * 4;
-  const int64_t row = m0 + e / BN, col = n0 + e % BN;
-  if (row >= M || col >= N) return;
-  floatx4 s = {0.f, 0.f, 0.f, 0.f};
+}
+
+// Sum of every ragged tile's partial tiles, in K order, and the epilogue.
+// One float4 of the partials (four rows of a column) per thread; a wave's
+// stores cover 128-byte runs of two rows.
+template <int WM, int WN, int NWM, int NWN>
+__global__ __launch_bounds__(256) void gemm_fixup(int64_t M, int64_t N, int64_t msplit, SSched S,
+                                                        const float* __restrict__ partials, SOut C) {
+  constexpr int BM = 32 * WM * NWM, BN = 32 * WN * NWN;
+  const int64_t rt = blockIdx.x;
+  const TilePos tp = tile_pos<BM, BN>(S, M, msplit, S.whole + rt);
+  const int64_t mlim = tp.mlim, grp = tp.grp;
+  const int e = blockIdx.y * 256 + threadIdx.x;
+  const int lane = e & 63, r4 = (e >> 6) & 3, blk = e >> 8;
+  const int wave = blk / (WM * WN), ab = blk % (WM * WN);
+  const int64_t row = tp.m0 + ((wave / NWN) * WM + ab / WN) * 32 + 8 * r4 + 4 * (lane >> 5);
+  const int64_t col = tp.n0 + ((wave % NWN) * WN + ab % WN) * 32 + (lane & 31);
+  if (row >= mlim || col >= N) return;
+  int parts = S.full;
+  if (S.rem > 0)
+    parts += static_cast<int>(((rt + 1) * S.rem - 1) / S.ipw - (rt * S.rem) / S.ipw) + 1;
+  const floatx4* p = reinterpret_cast<const floatx4*>(partials + rt * S.parts * static_cast<int64_t>(BM * BN)) + e;
+  floatx4 s = *p;
 #pragma unroll 4
-  for (int j = 0; j < parts; ++j) s += *reinterpret_cast<const floatx4*>(partials + slot_off[j] + e);
+  for (int q = 1; q < parts; ++q) s += p[q * (BM * BN / 4)];
+  SOut Cg = C;
+  Cg.c0 += grp * C.gs0;
+  Cg.c1 += grp * C.gs1;
+  if (C.mask) Cg.mask += grp * C.gsm;
 #pragma unroll
   for (int q = 0; q < 4; ++q)
-    if (col + q < N) store_out(Cg, row, col + q, s[q]);
+    if (row + q < mlim) s_store(Cg, row + q, col, s[q]);
 }
 
-constexpr int64_t kStreamWG = 512;   // two resident 256-thread blocks per CU, 256 CUs
-constexpr int64_t kMinSteps = 8;     // fewest K steps a stream-K workgroup takes
+// ---- host side ---------------------------------------------------------------
 
-Sched make_sched(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups = 1) {
-  const int ks = dtype == GIST_DTYPE_BF16_IN ? KSH : BK;
-  Sched s;
-  s.tiles_m = static_cast<int>((M + BM - 1) / BM);
-  s.tiles_n = static_cast<int>((N + BN - 1) / BN);
-  s.nk = static_cast<int>((K + ks - 1) / ks);
-  s.tpg = static_cast<int64_t>(s.tiles_m) * s.tiles_n;
-  const int64_t tiles = s.tpg * groups;
-  s.tiles = tiles;
-  s.T = tiles * s.nk;
-  s.spu = 0;
-  if (tiles >= 4 * kStreamWG) {
-    s.ipw = s.nk;   // enough tiles: one whole tile per workgroup
-  } else if (tiles * 8 <= kStreamWG && s.nk >= 2 * kMinSteps) {
-    // few tiles, long K (a weight gradient over many nodes): the K range in
-    // slices, K-slice-major over the grid, at least kMinSteps steps each
-    const int64_t slices = std::min<int64_t>(kStreamWG / tiles, s.nk / kMinSteps);
-    s.spu = (s.nk + slices - 1) / slices;
-    s.ipw = s.spu;
-  } else {
-    // stream-K over kStreamWG workgroups, but at least kMinSteps K steps
-    // each: a small product (a narrow slice, few tiles) split one step per
-    // workgroup would write a 64 KB partial tile per step for the fix-up to
-    // read back
-    s.ipw = std::max<int64_t>((s.T + kStreamWG - 1) / kStreamWG,
-                              std::min<int64_t>(s.nk, kMinSteps));
+struct Cfg {
+  int bm, bn, kw;     // tile, K per step
+  int per_cu;         // workgroups a CU holds at once
+  int min_steps;      // fewest steps worth a workgroup of their own
+  int max_run;        // most steps a workgroup accumulates (4,096 values of K)
+  double step_us;     // one step of one workgroup with per_cu of them on every CU
+  double alone_us;    // the least a step takes (memory latency)
+  double fixed_us;    // a workgroup's first loads and its stores
+};
+// 0..2: fp32; 3..4: bf16 inputs.  The times were measured with the machine full
+// (256 x 256: 102 steps over 512 tiles in 572 us; 128 x 128: 102 steps over
+// 2,048 tiles in 658; 64 x 64: 8 steps over 2,504 tiles in 112) and nearly
+// empty; choose_cfg takes the shape whose estimate is lowest.  Where two
+// are close: 3,100 x 1,024 over K = 1,204 takes 72.0 / 72.6 / 89 us with the
+// three fp32 tiles, 1,630 x 8,192 over K = 47 24 / 30 / 42, 2,000 x 128 over
+// K = 1,433 32 / 21 / 23, 3,100 x 64 over K = 602 35 / 21 / 12.
+constexpr Cfg kCfg[] = {{256, 256, 16, 1, 8, 256, 2.7, 1.6, 14.0},
+                        {128, 128, 16, 2, 8, 256, 1.5, 0.8, 7.0},
+                        {64, 64, 64, 3, 2, 64, 3.5, 1.0, 4.0},
+                        {128, 128, 64, 2, 2, 1 << 20, 2.0, 1.0, 7.0},
+                        {64, 64, 64, 3, 2, 1 << 20, 1.8, 0.8, 4.0}};
+constexpr int64_t kCUs = 256;
+constexpr int64_t kMaxLd = int64_t(1) << 22;   // 255 rows of it in 32 bits of bytes
+
+// Time of `units` workgroups of `steps` steps: whole rounds of full CUs,
+// then a round with fewer workgroups on each CU.
+double run_us(const Cfg& c, int64_t units, int steps) {
+  const int64_t slots = kCUs * c.per_cu, rounds = units / slots, rest = units % slots;
+  double us = rounds * (steps * c.step_us + c.fixed_us);
+  if (rest > 0) {
+    const double share = static_cast<double>((rest + kCUs - 1) / kCUs) / c.per_cu;
+    us += steps * std::max(c.alone_us, c.step_us * share) + c.fixed_us;
   }
+  return us;
+}
+
+SSched make_ssched(int64_t M, int64_t N, int64_t K, int64_t groups, int64_t msplit, int64_t ksplit,
+                   const Cfg& c, double* cost) {
+  SSched s{};
+  s.tm0 = static_cast<int>((msplit + c.bm - 1) / c.bm);
+  s.tiles_m = s.tm0 + static_cast<int>((M - msplit + c.bm - 1) / c.bm);
+  s.tiles_n = static_cast<int>((N + c.bn - 1) / c.bn);
+  s.nf0 = static_cast<int>(ksplit / c.kw);
+  s.nf = s.nf0 + static_cast<int>((K - ksplit) / c.kw);
+  s.nk = s.nf + (ksplit % c.kw != 0) + ((K - ksplit) % c.kw != 0);
+  s.tpg = static_cast<int64_t>(s.tiles_m) * s.tiles_n;
+  s.tiles = s.tpg * groups;
+  s.whole = s.tiles;
+  s.full = 1;
+  s.ipw = s.nk;
+  // K cut into parts: `ipw` steps each, at most c.max_run
+  auto cut = [&](int64_t tiles, int ipw) {
+    int full = s.nk / ipw, rem = s.nk - full * ipw;
+    if (rem > 0 && (rem < c.min_steps / 2 || ipw == c.max_run)) {   // no sliver per tile; equal parts of a long K
+      const int q = rem < c.min_steps / 2 && (s.nk + full - 1) / full <= c.max_run ? full : full + 1;
+      ipw = (s.nk + q - 1) / q;
+      full = s.nk / ipw;
+      rem = s.nk - full * ipw;
+    }
+    s.ragged = tiles;
+    s.whole = s.tiles - tiles;
+    s.full = full;
+    s.ipw = ipw;
+    s.rem = rem;
+    s.parts = full + (rem > 0 ? 2 : 0);
+  };
+  // time of writing and summing the parts
+  auto fix_us = [&]() {
+    return s.ragged ? 5.0 + 2.0 * s.ragged * (s.full + (s.rem > 0 ? 1.3 : 0.0)) * c.bm * c.bn * 4.0 / 5.0e6
+                    : 0.0;
+  };
+  const int64_t slots = kCUs * c.per_cu;
+  const int64_t waves = s.tiles / slots, r = s.tiles - waves * slots;
+  auto units = [&]() {
+    return s.ragged * s.full + (s.rem > 0 ? (s.ragged * s.rem + s.ipw - 1) / s.ipw : 0);
+  };
+  double us;
+  if (s.nk > c.max_run) {
+    const int even = static_cast<int>(std::max<int64_t>((s.tiles * s.nk + slots - 1) / slots, c.min_steps));
+    cut(s.tiles, std::min(even, c.max_run));
+    us = run_us(c, units(), s.ipw) + fix_us();
+  } else {
+    us = run_us(c, s.tiles, s.nk);
+    const int ipw = static_cast<int>(std::max<int64_t>((r * s.nk + slots - 1) / slots, c.min_steps));
+    if (r > 0 && ipw < s.nk) {   // the last, partly filled round cut in K, if that is quicker
+      const SSched keep = s;
+      cut(r, ipw);
+      const double t = run_us(c, waves * slots, s.nk) + run_us(c, units(), s.ipw) + fix_us();
+      if (t < us && s.ipw < s.nk) us = t;
+      else s = keep;
+    }
+  }
+  if (cost) *cost = us;
   return s;
 }
 
-int64_t sched_slices(const Sched& s) { return (s.nk + s.spu - 1) / s.spu; }
-int64_t sched_groups(const Sched& s) {
-  return s.spu > 0 ? sched_slices(s) * s.tiles : (s.T + s.ipw - 1) / s.ipw;
-}
-bool sched_split(const Sched& s) { return s.spu > 0 ? sched_slices(s) > 1 : s.ipw % s.nk != 0; }
-
-// 16-byte loads along the operand's contiguous dimension are legal when the
-// leading dimensions and base addresses are multiples of 4 floats (and, for
-// row-contiguous operands, the row count too).  A concatenation split must
-// fall on a 128 boundary, so that every K step and every tile lies on one
-// side of it and the pointer choice stays uniform.
-bool op_vec_ok(const Operand& o, int64_t R) {
-  if (o.ld0 % 4 || !aligned16(o.p0) || o.gs0 % 4) return false;
-  if (o.p1 && (o.ld1 % 4 || !aligned16(o.p1) || o.split % 128 || o.gs1 % 4)) return false;
-  if (!o.k_major && R % 4) return false;
-  return true;
+int choose_cfg(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups, int64_t msplit, int64_t ksplit) {
+  const int lo = dtype == GIST_DTYPE_BF16_IN ? 3 : 0, hi = dtype == GIST_DTYPE_BF16_IN ? 5 : 3;
+  int best = lo;
+  double bc = 1e300;
+  for (int i = lo; i < hi; ++i) {
+    double c;
+    make_ssched(M, N, K, groups, msplit, ksplit, kCfg[i], &c);
+    if (c < bc) { bc = c; best = i; }
+  }
+  return best;
 }
 
-template <bool AK, bool BK_, bool BF16, bool NARROW>
-void launch_kernel(hipStream_t st, bool av, bool bv, dim3 grid, int64_t M, int64_t N, int64_t K,
-                   const OpDev& A, const OpDev& B, const OutDev& C, const Sched& S,
-                   float* part) {
-#define GIST_GEMM_LAUNCH(AV_, BV_)                                                         \
-  hipLaunchKernelGGL((gemm_kernel<AK, BK_, AV_, BV_, BF16, NARROW>), grid, dim3(kThreads), 0, \
-                     st, M, N, K, A, B, C, S, part)
-  if (av && bv) GIST_GEMM_LAUNCH(true, true);
-  else if (av) GIST_GEMM_LAUNCH(true, false);
-  else if (bv) GIST_GEMM_LAUNCH(false, true);
-  else GIST_GEMM_LAUNCH(false, false);
-#undef GIST_GEMM_LAUNCH
+int64_t sgrid(const SSched& s) {
+  return s.whole + s.ragged * s.full + (s.rem > 0 ? (s.ragged * s.rem + s.ipw - 1) / s.ipw : 0);
 }
 
-template <bool BF16, bool NARROW>
-void dispatch(hipStream_t st, const Operand& A, const Operand& B, bool av, bool bv, dim3 grid,
-              int64_t M, int64_t N, int64_t K, const OpDev& a, const OpDev& b, const OutDev& c,
-              const Sched& S, float* part) {
-  if (A.k_major && B.k_major)
-    launch_kernel<true, true, BF16, NARROW>(st, av, bv, grid, M, N, K, a, b, c, S, part);
-  else if (A.k_major)
-    launch_kernel<true, false, BF16, NARROW>(st, av, bv, grid, M, N, K, a, b, c, S, part);
-  else if (B.k_major)
-    launch_kernel<false, true, BF16, NARROW>(st, av, bv, grid, M, N, K, a, b, c, S, part);
-  else
-    launch_kernel<false, false, BF16, NARROW>(st, av, bv, grid, M, N, K, a, b, c, S, part);
+// Floats per load along the operand's contiguous dimension (4, 2 or 1).
+int vec_of(const Operand& o, int64_t R, int64_t K) {
+  const bool k = o.k_major;
+  const int64_t ext = k ? K : R;
+  const int64_t sp = o.p1 ? o.split : ext;
+  for (int v = 4; v > 1; v >>= 1) {
+    if (!k && v == 4) continue;
+    const uintptr_t m = 4 * v - 1;
+    if (o.ld0 % v == 0 && ext % v == 0 && sp % v == 0 && o.gs0 % v == 0 &&
+        !(reinterpret_cast<uintptr_t>(o.p0) & m) &&
+        (!o.p1 || (!(reinterpret_cast<uintptr_t>(o.p1) & m) && o.gs1 % v == 0)))
+      return k ? v : 4;
+  }
+  return 1;
 }
 
 }  // namespace
 
-size_t gemm_workspace(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups) {
+size_t gemm_workspace(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups, int64_t msplit,
+                      int64_t ksplit) {
   if (M <= 0 || N <= 0 || K <= 0 || groups <= 0) return 0;
   if (dtype == GIST_DTYPE_BF16_IN && gemm_bf16_packed_eligible(M, N, K))
     return gemm_bf16_packed_workspace(M, N, K);   // groups run one after another
-  const Sched s = make_sched(M, N, K, dtype, groups);
-  if (!sched_split(s)) return 0;
-  return static_cast<size_t>(sched_groups(s)) * 2 * BM * BN * sizeof(float);
+  if (msplit <= 0) msplit = M;
+  if (ksplit <= 0) ksplit = K;
+  const Cfg& c = kCfg[choose_cfg(M, N, K, dtype, groups, msplit, ksplit)];
+  const SSched s = make_ssched(M, N, K, groups, msplit, ksplit, c, nullptr);
+  return static_cast<size_t>(s.ragged) * s.parts * c.bm * c.bn * sizeof(float);
 }
 
-gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K, const Operand& A,
-                 const Operand& B, const GemmOut& C, int dtype, void* ws, size_t ws_bytes,
-                 int64_t ngroups, int64_t k_alg) {
-  if (M <= 0 || N <= 0 || ngroups <= 0) return GIST_OK;
-  OutDev c{C.c0, C.c1, C.ldc0, C.ldc1, C.c_split, C.relu ? 1 : 0, C.gs0, C.gs1,
-           C.sgd ? 1 : 0, C.lr, C.mask, C.ldm, C.gsm};
+gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K, const Operand& A, const Operand& B,
+                 const GemmOut& C, int dtype, void* ws, size_t ws_bytes, int64_t groups) {
+  if (M <= 0 || N <= 0 || groups <= 0) return GIST_OK;
   if (K <= 0) return set_error(GIST_E_UNSUPPORTED, "gemm: K == 0");
-  if (dtype == GIST_DTYPE_BF16_IN && gemm_bf16_packed_eligible(M, N, K)) {
+  const bool bf = dtype == GIST_DTYPE_BF16_IN;
+  if (bf && gemm_bf16_packed_eligible(M, N, K)) {
     // the packed path converts each group's operands; groups run in turn
-    for (int64_t g = 0; g < ngroups; ++g) {
+    for (int64_t g = 0; g < groups; ++g) {
       Operand ag = A, bg = B;
       GemmOut cg = C;
       ag.p0 += g * A.gs0;
@@ -789,64 +1029,87 @@ gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K, const Operand&
       cg.c0 += g * C.gs0;
       if (C.c1) cg.c1 += g * C.gs1;
       if (C.mask) cg.mask += g * C.gsm;
-      gist_status s = gemm_bf16_packed(st, M, N, K, ag, bg, cg, ws, ws_bytes);
-      if (s != GIST_OK) return s;
+      const gist_status r = gemm_bf16_packed(st, M, N, K, ag, bg, cg, ws, ws_bytes);
+      if (r != GIST_OK) return r;
     }
     return GIST_OK;
   }
-  if (K > (static_cast<int64_t>(INT32_MAX) - KSH) * BK)
+  if (K > static_cast<int64_t>(INT32_MAX - 2) * KS)
     return set_error(GIST_E_UNSUPPORTED, "gemm: K too large");
-  const Sched S = make_sched(M, N, K, dtype, ngroups);
-  const int64_t groups = sched_groups(S);
-  const int64_t tiles = S.tpg * ngroups;
-  if (groups > INT32_MAX || tiles > INT32_MAX)
-    return set_error(GIST_E_UNSUPPORTED, "gemm: grid too large");
-  float* part = nullptr;
-  const bool split = sched_split(S);
-  if (split) {
-    // a tile's iterations span at most ceil(nk / ipw) + 1 workgroups
-    if ((S.spu > 0 ? sched_slices(S) : (S.nk + S.ipw - 1) / S.ipw + 1) > kMaxFixupParts)
-      return set_error(GIST_E_UNSUPPORTED, "gemm: too many partial tiles per tile");
-    const size_t need = gemm_workspace(M, N, K, dtype, ngroups);
-    if (!ws || ws_bytes < need) return set_error(GIST_E_NOMEM, "gemm: workspace too small");
-    part = static_cast<float*>(ws);
+  if ((!A.k_major && B.k_major) || (A.p1 && A.ld1 != A.ld0) || B.p1)
+    return set_error(GIST_E_UNSUPPORTED, "gemm: operand form");
+  const int64_t msplit = !A.k_major && A.p1 ? std::min(A.split, M) : M;
+  const int64_t ksplit = A.k_major && A.p1 ? std::min(A.split, K) : K;
+  int ci = choose_cfg(M, N, K, dtype, groups, msplit, ksplit);
+  // 32-bit offsets inside a tile; past them the small kernel, which has 64-bit
+  // ones, with whole tiles
+  const bool far = ci < 2 && (A.ld0 >= kMaxLd || B.ld0 >= kMaxLd);
+  if (far) ci = 2;
+  const Cfg& c = kCfg[ci];
+  SSched s = make_ssched(M, N, K, groups, msplit, ksplit, c, nullptr);
+  if (far) {
+    s.whole = s.tiles;
+    s.ragged = s.parts = s.rem = 0;
   }
-  OpDev a{A.p0, A.p1 ? A.p1 : A.p0, A.ld0, A.p1 ? A.ld1 : A.ld0, A.p1 ? A.split : INT64_MAX,
-          A.gs0, A.p1 ? A.gs1 : A.gs0};
-  OpDev b{B.p0, B.p1 ? B.p1 : B.p0, B.ld0, B.p1 ? B.ld1 : B.ld0, B.p1 ? B.split : INT64_MAX,
-          B.gs0, B.p1 ? B.gs1 : B.gs0};
-  const bool bf = dtype == GIST_DTYPE_BF16_IN;
-  const bool av = op_vec_ok(A, M);
-  const bool bv = op_vec_ok(B, N);
-  const bool narrow = !bf && N <= BN / 2;
-  dim3 grid(static_cast<unsigned>(groups));
+  const size_t need = static_cast<size_t>(s.ragged) * s.parts * c.bm * c.bn * sizeof(float);
+  if (need > 0 && (!ws || ws_bytes < need))
+    return set_error(GIST_E_NOMEM, "gemm: workspace too small");
+  const int64_t grid = sgrid(s);
+  if (grid > INT32_MAX || s.tiles > INT32_MAX) return set_error(GIST_E_UNSUPPORTED, "gemm: grid too large");
+  SOp a{A.p0, A.p1 ? A.p1 : A.p0, A.ld0, A.gs0, A.p1 ? A.gs1 : A.gs0};
+  SOp b{B.p0, B.p0, B.ld0, B.gs0, B.gs0};
+  SOut o{C.c0, C.c1, C.ldc0, C.ldc1, C.c_split, C.gs0, C.gs1, C.mask, C.ldm, C.gsm, C.lr,
+         C.relu ? 1 : 0, C.sgd ? 1 : 0};
+  const int v = std::min(vec_of(A, M, K), vec_of(B, N, K));
+  float* part = static_cast<float*>(ws);
   {
     // variant name: dtype, the K-contiguous (K) / row-contiguous (R)
-    // orientation of A and B as read from memory, whether each is read
-    // with 16-byte vector loads (v) or scalar loads (s), and _n for the
-    // narrow split -- one name per kernel instantiation
-    char name[32];
-    snprintf(name, sizeof(name), "gemm_%s_%c%c_%c%c%s", bf ? "bf16" : "f32",
-             A.k_major ? 'K' : 'R', B.k_major ? 'K' : 'R', av ? 'v' : 's', bv ? 'v' : 's',
-             narrow ? "_n" : "");
-    const double md = static_cast<double>(M), nd = static_cast<double>(N),
-                 kd = static_cast<double>(k_alg > 0 ? k_alg : K);
-    const double gd = static_cast<double>(ngroups);
+    // orientation of A and B, the tile, and the floats per load
+    char name[48];
+    snprintf(name, sizeof(name), "gemm_%s_%c%c_%dx%d_v%d", bf ? "bf16" : "f32", A.k_major ? 'K' : 'R',
+             B.k_major ? 'K' : 'R', c.bm, c.bn, v);
+    const double md = static_cast<double>(M), nd = static_cast<double>(N), kd = static_cast<double>(K),
+                 gd = static_cast<double>(groups);
     ProfScope ps(st, name, 2.0 * md * nd * kd * gd, 4.0 * (md * kd + kd * nd + md * nd) * gd);
-    if (bf) dispatch<true, false>(st, A, B, av, bv, grid, M, N, K, a, b, c, S, part);
-    else if (narrow) dispatch<false, true>(st, A, B, av, bv, grid, M, N, K, a, b, c, S, part);
-    else dispatch<false, false>(st, A, B, av, bv, grid, M, N, K, a, b, c, S, part);
+    const dim3 g(static_cast<unsigned>(grid));
+#define GIST_ARGS g, dim3(thr), 0, st, M, N, K, msplit, ksplit, a, b, o, s, part
+#define GIST_SPLIT(AK_, BK_, V_)                                                                             \
+  do {                                                                                                       \
+    const unsigned thr = ci == 0 ? 512 : 256;                                                                \
+    if (ci == 0) hipLaunchKernelGGL((gemm_split_kernel<2, 4, 4, 2, AK_, BK_, V_>), GIST_ARGS);               \
+    else if (ci == 1) hipLaunchKernelGGL((gemm_split_kernel<2, 2, 2, 2, AK_, BK_, V_>), GIST_ARGS);          \
+    else if (ci == 2) hipLaunchKernelGGL((gemm_small_kernel<3, 1, 1, AK_, BK_, V_>), GIST_ARGS);             \
+    else if (ci == 3) hipLaunchKernelGGL((gemm_small_kernel<1, 2, 2, AK_, BK_, V_>), GIST_ARGS);             \
+    else hipLaunchKernelGGL((gemm_small_kernel<1, 1, 1, AK_, BK_, V_>), GIST_ARGS);                          \
+  } while (0)
+#define GIST_SPLIT_V(AK_, BK_)             \
+  do {                                     \
+    if (v == 4) GIST_SPLIT(AK_, BK_, 4);   \
+    else if (v == 2) GIST_SPLIT(AK_, BK_, 2); \
+    else GIST_SPLIT(AK_, BK_, 1);          \
+  } while (0)
+    if (A.k_major && B.k_major) GIST_SPLIT_V(true, true);
+    else if (A.k_major) GIST_SPLIT_V(true, false);
+    else GIST_SPLIT_V(false, false);
+#undef GIST_SPLIT_V
+#undef GIST_SPLIT
+#undef GIST_ARGS
   }
   {
-    gist_status s = check_launch("gemm");
-    if (s != GIST_OK) return s;
+    const gist_status r = check_launch("gemm");
+    if (r != GIST_OK) return r;
   }
-  if (split) {
-    ProfScope ps(st, "gemm_streamk_fixup", 0.0,
-                 4.0 * static_cast<double>(groups) * 2 * BM * BN + 4.0 * M * N * ngroups);
-    hipLaunchKernelGGL(streamk_fixup, dim3(static_cast<unsigned>(tiles), kFixChunks), dim3(256), 0,
-                       st, M, N, S, part, c);
-    return check_launch("gemm stream-K fix-up");
+  if (s.ragged > 0) {
+    ProfScope ps(st, "gemm_fixup", 0.0,
+                 4.0 * s.ragged * static_cast<double>(c.bm) * c.bn * (s.full + 1.3 * (s.rem > 0) + 1.0));
+    const dim3 g(static_cast<unsigned>(s.ragged), static_cast<unsigned>(c.bm * c.bn / 1024));
+    if (ci == 0)
+      hipLaunchKernelGGL((gemm_fixup<2, 4, 4, 2>), g, dim3(256), 0, st, M, N, msplit, s, part, o);
+    else if (c.bm == 128)
+      hipLaunchKernelGGL((gemm_fixup<2, 2, 2, 2>), g, dim3(256), 0, st, M, N, msplit, s, part, o);
+    else
+      hipLaunchKernelGGL((gemm_fixup<1, 1, 2, 2>), g, dim3(256), 0, st, M, N, msplit, s, part, o);
+    return check_launch("gemm fix-up");
   }
   return GIST_OK;
 }

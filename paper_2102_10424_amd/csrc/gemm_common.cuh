@@ -89,6 +89,14 @@ __device__ __forceinline__ void tile_coords_banded(int64_t t, int tiles_m, int t
   tn = static_cast<int>(in_band / rows_in_band);
 }
 
+// Workgroup barrier that orders LDS only: waits for this wave's LDS
+// accesses, not its global loads, so prefetches stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 bool gemm_bf16_packed_eligible(int64_t M, int64_t N, int64_t K);
 size_t gemm_bf16_packed_workspace(int64_t M, int64_t N, int64_t K);
 gist_status gemm_bf16_packed(hipStream_t st, int64_t M, int64_t N, int64_t K, const Operand& A,

@@ -147,13 +147,16 @@ struct GemmOut {
 };
 
 // `groups` independent products of the same shape: group g reads A and B
-// and writes C at the pointers offset by g times their group strides.
-size_t gemm_workspace(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups = 1);
-// k_alg: the reduction length the profiler counts (flops, bytes) when K
-// includes zero padding (0: K itself).
+// and writes C at the pointers offset by g times their group strides.  A may
+// be a concatenation (p1) with ld1 == ld0, B may not; a row-contiguous A goes
+// with a row-contiguous B.  The workspace depends on where A is concatenated:
+// msplit rows (a row-contiguous A) or ksplit values of K in its first part
+// (0: not concatenated).
+size_t gemm_workspace(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups = 1, int64_t msplit = 0,
+                      int64_t ksplit = 0);
 gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K,
                  const Operand& A, const Operand& B, const GemmOut& C, int dtype,
-                 void* ws, size_t ws_bytes, int64_t groups = 1, int64_t k_alg = 0);
+                 void* ws, size_t ws_bytes, int64_t groups = 1);
 
 // dZ[i] = dH[i] * (Hout[i] > 0) over n x w (ld = w).
 gist_status relu_mask(hipStream_t st, int64_t count, const float* dH,
@@ -168,10 +171,6 @@ gist_status scatter(hipStream_t st, float* Wg, int64_t ldg, const int32_t* rows,
 gist_status count_nonfinite(hipStream_t st, const float* Ws, int64_t lds,
                             int32_t nr, int32_t nc, int* d_count);
 gist_status fill_zero(hipStream_t st, float* p, int64_t count);
-// dst (cols x rows, ld ldd >= rows) = src^T (src rows x cols, ld lds); columns
-// rows .. ldd-1 of every dst row are set to zero.
-gist_status transpose(hipStream_t st, const float* src, int64_t rows, int64_t cols, int64_t lds,
-                      float* dst, int64_t ldd);
 // dst <- src (bytes), by a kernel on the stream; src may be pinned host memory.
 gist_status pull_copy(hipStream_t st, void* dst, const void* src, int64_t bytes);
 gist_status subagg_gather(hipStream_t st, float* Wg, int64_t rows, int64_t cols, int64_t ldg,
