@@ -32,9 +32,10 @@
 // straight from memory; finite inputs never take that path unless the
 // product overflows.
 //
-// bf16-input products with M or N below 512 run here too (one product of the
-// rounded operands, gemm_small_kernel<1, ...>); larger ones in gemm_bf16.hip.
-//
+// bf16-input products round the operands (nearest even) on the same way to LDS
+// and take one product: gemm_bf16_kernel (256 x 256 tiles) and
+// gemm_small_kernel<1, ...>.
+
 // Work distribution: tiles are whole where there are enough of them.  The
 // tiles of the last, partly filled round (or all, where K is beyond 4,096)
 // are cut in K, all at the same steps, slice-major, so that the workgroups an
@@ -48,7 +49,6 @@
 #include <type_traits>
 
 #include "common.cuh"
-#include "gemm_common.cuh"
 #include "gist_internal.h"
 
 namespace gist {
@@ -61,6 +61,26 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+
+// Tile id -> (tile_m, tile_n): column-major in bands of 8 tile rows, so the
+// tiles an XCD runs together share B columns and a narrow band of A rows.
+__device__ __forceinline__ void tile_coords_banded(int64_t t, int tiles_m, int tiles_n, int& tm,
+                                                   int& tn) {
+  constexpr int kBand = 8;
+  const int band = static_cast<int>(t / (static_cast<int64_t>(kBand) * tiles_n));
+  const int rows_in_band = min(kBand, tiles_m - band * kBand);
+  const int64_t in_band = t - static_cast<int64_t>(band) * kBand * tiles_n;
+  tm = band * kBand + static_cast<int>(in_band % rows_in_band);
+  tn = static_cast<int>(in_band / rows_in_band);
+}
+
+// Workgroup barrier that orders LDS only: waits for this wave's LDS
+// accesses, not its global loads, so prefetches stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 constexpr int KS = 16;         // K per step: one bf16 MFMA
 
@@ -119,11 +139,15 @@ __device__ __forceinline__ void split4(const float (&x)[4], uintx2 (&pl)[NP]) {
   }
 }
 
-// LDS tile of one operand: plane-major, then blocks of 32 rows: 16-byte
-// chunks (8 K) q = 0, 1 of the 32 rows, 1 KB per block.  The row order inside
-// a block makes the fragment reads and both kinds of staging writes free of
-// bank conflicts.
-__device__ __forceinline__ int lds_slot(int r, int q) { return (r ^ ((r >> 3) & 1)) ^ (q * 4); }
+// LDS tile of one operand: 16-K chunks, planes, then blocks of 32 rows:
+// 16-byte pieces (8 K) q = 0, 1 of the 32 rows, 1 KB per block.  The order of
+// the rows inside a block, which also depends on the chunk c, spreads the
+// fragment reads (32 rows, one piece) and the 8-byte staging writes (lanes along
+// K, or along the rows in steps of one, two or four) over the banks.
+__device__ __forceinline__ int lds_slot(int r, int q) {
+  return r ^ ((r >> 3) & 1) ^ (((r >> 4) & 1) << 1) ^ (q * 4);
+}
+__host__ __device__ constexpr int chunk_xor(int c) { return (((c & 1) << 1) | ((c >> 1) & 1)) * 16; }
 template <int ROWS>
 __device__ __forceinline__ int lds_off(int row, int q) {
   return (row >> 5) * 1024 + q * 512 + lds_slot(row & 31, q) * 16;
@@ -132,15 +156,18 @@ template <int ROWS>
 constexpr int plane_bytes() { return ROWS * 32; }
 
 // One operand's share of a K step, held in registers between its load and
-// its split.  Groups of four consecutive K of one row.
-//   K contiguous: row (t >> 2) + 64 i, K 4 (t & 3): V = 4, 2 or 1 floats per load.
-//   Row contiguous, V >= 2: two rows by four K, one 8-byte load per K.
-//   Row contiguous, V = 1: one row by four K.
+// its split.  Groups of four consecutive K of one row, in load items:
+//   K contiguous: one group, V = 4, 2 or 1 floats per load;
+//   row contiguous: R rows by four K, one load of R floats per K, R = 4 or 2
+//     where the alignment allows.
+// The load path takes four lanes per clock whatever their width (a wave's
+// 8-byte load took 19 clocks, its 16-byte load 20), so loads are as wide as
+// they can be; steps of 16 K leave only eight floats per thread, hence R = 2.
 template <int NP, bool KM, int V, int ROWS, int THR, int KW, typename OFF>
 struct Stage {
   static constexpr int NG = ROWS * (KW / 4) / THR;     // groups per thread
-  static constexpr bool PAIR = !KM && V >= 2 && KW == 16;
-  static constexpr int GP = PAIR ? 2 : 1;              // groups per load item
+  static constexpr int R = KM ? 1 : V >= 4 && KW >= 32 ? 4 : V >= 2 && NG >= 2 ? 2 : 1;
+  static constexpr int GP = R;                         // groups per load item
   static constexpr int NI = NG / GP;
   float v[NG][4];
   OFF off[NI];
@@ -149,9 +176,7 @@ struct Stage {
     const int x = t + THR * i;
     constexpr int L = KW / 4;   // lanes per row
     if constexpr (KM) { row = t / L + (THR / L) * i; kk = 4 * (t % L); }
-    else if constexpr (PAIR) { row = 2 * ((x >> 1) % (ROWS / 2)); kk = 8 * (x / ROWS) + 4 * (x & 1); }
-    else if constexpr (KW == 16) { row = (x >> 1) % ROWS; kk = 8 * (x / (2 * ROWS)) + 4 * (x & 1); }
-    else { row = x % ROWS; kk = 4 * (x / ROWS); }
+    else { row = R * (x % (ROWS / R)); kk = 4 * (x / (ROWS / R)); }
   }
   __device__ __forceinline__ void init(int64_t ld, int rows_left, int t) {
 #pragma unroll
@@ -161,7 +186,7 @@ struct Stage {
       if constexpr (KM)
         off[i] = static_cast<OFF>(min(row, rows_left - 1)) * static_cast<OFF>(ld * 4) + 4 * kk;
       else
-        off[i] = static_cast<OFF>(4 * min(row, rows_left - (PAIR ? 2 : 1))) +
+        off[i] = static_cast<OFF>(4 * min(row, rows_left - R)) +
                  static_cast<OFF>(kk) * static_cast<OFF>(ld * 4);
     }
   }
@@ -194,7 +219,11 @@ struct Stage {
         for (int j = 0; j < 4; ++j) {
           const char* p = EDGE ? base + (off[i] + static_cast<OFF>(min(kk + j, klim - 1) - kk) * ld4)
                                : base + j * static_cast<int64_t>(ld4) + off[i];
-          if constexpr (PAIR) {
+          if constexpr (R == 4) {
+            const floatx4 x = *reinterpret_cast<const floatx4*>(p);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[4 * i + q][j] = x[q];
+          } else if constexpr (R == 2) {
             const floatx2 x = *reinterpret_cast<const floatx2*>(p);
             v[2 * i][j] = x[0];
             v[2 * i + 1][j] = x[1];
@@ -211,7 +240,7 @@ struct Stage {
   __device__ __forceinline__ void store(char* S, int g, int klim, float sg, int t) const {
     int row, kk;
     item(t, g / GP, row, kk);
-    if constexpr (PAIR) row += g & 1;
+    if constexpr (R > 1) row += g % R;
     float x[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -220,7 +249,8 @@ struct Stage {
     }
     uintx2 pl[NP];
     split4<NP>(x, pl);
-    char* d = S + (KW > 16 ? (kk >> 4) * (NP * plane_bytes<ROWS>()) : 0) + lds_off<ROWS>(row, (kk >> 3) & 1) +
+    const int c = KW > 16 ? kk >> 4 : 0;
+    char* d = S + c * (NP * plane_bytes<ROWS>()) + (lds_off<ROWS>(row, (kk >> 3) & 1) ^ chunk_xor(c)) +
               ((kk >> 2) & 1) * 8;
 #pragma unroll
     for (int p = 0; p < NP; ++p) *reinterpret_cast<uintx2*>(d + p * plane_bytes<ROWS>()) = pl[p];
@@ -796,11 +826,11 @@ __global__ __launch_bounds__(256, WM == 1 ? 3 : 2) void gemm_small_kernel(
 #pragma unroll
           for (int a = 0; a < WM; ++a)
             av[a][p] = *reinterpret_cast<const bf16x8*>(lds + c * CA + p * plane_bytes<BM>() +
-                                                        (wm * WM + a) * 1024 + frag);
+                                                        (wm * WM + a) * 1024 + (frag ^ chunk_xor(c)));
 #pragma unroll
           for (int b = 0; b < WN; ++b)
             bv[b][p] = *reinterpret_cast<const bf16x8*>(ldsB + c * CB + p * plane_bytes<BN>() +
-                                                        (wn * WN + b) * 1024 + frag);
+                                                        (wn * WN + b) * 1024 + (frag ^ chunk_xor(c)));
         }
 #pragma unroll
         for (int a = 0; a < WM; ++a)
@@ -831,6 +861,213 @@ __global__ __launch_bounds__(256, WM == 1 ? 3 : 2) void gemm_small_kernel(
       store_tile<WM, WN>(acc, C, grp, m0 + wm * WM * 32, tp.mlim, n0 + wn * WN * 32, N);
     else
       store_part<WM, WN>(acc, sg,
+                         partials + ((units.tile - S.whole) * S.parts + units.part) * static_cast<int64_t>(BM * BN),
+                         wave);
+  }
+}
+
+// Large products with bf16 inputs: 256 x 256 tiles by eight waves of 64 x 128,
+// K steps of 32, operands rounded to bf16 on the way to three LDS buffers.
+// What bounds it: the fp32 operands, 64 KB per step and CU through the load
+// path for 1,024 clocks of MFMAs per SIMD; that path is busy 70-80% of the
+// kernel.  A wave's load takes 16 to 20 clocks there whatever its width, so
+// both orientations load 16 bytes per lane: with 8-byte loads of a
+// row-contiguous operand dW took 190 us instead of 156, with the two 16-byte
+// halves of a lane's 32 bytes in turn (half lines) dH 167 instead of 150.
+// On a 4,096-wide GraphSAGE layer with 1,630 nodes (109 GFLOP each; forward,
+// dH, dW): 209 / 167 / 206 us -> 202 / 150 / 156; four sub-GCNs' 3,100 x 1,024
+// products over K = 2,048 in one grid instead of four: 340 -> 85 us.
+constexpr int KB = 32;
+template <bool AK, bool BK, int V>
+__global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(int64_t M, int64_t N, int64_t K, int64_t msplit,
+                                                           int64_t ksplit, SOp A, SOp B, SOut C, SSched S,
+                                                           float* __restrict__ partials) {
+  constexpr int WM = 2, WN = 4, NWN = 2, THR = 512, BM = 256, BN = 256;
+  constexpr int CA = plane_bytes<BM>(), CB = plane_bytes<BN>();   // bytes of 16 K
+  __shared__ __attribute__((aligned(16))) char lds[3][2 * (CA + CB)];
+  using SA = Stage<1, AK, V, BM, THR, KB, unsigned>;
+  using SB = Stage<1, BK, V, BN, THR, KB, unsigned>;
+  const int t = threadIdx.x;
+  const int lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wave / NWN, wn = wave % NWN;
+  const int frag = (lane >> 5) * 512 + lds_slot(lane & 31, lane >> 5) * 16;
+  floatx16 acc[WM][WN];
+  SA sa;
+  SB sb;
+  Units units(S);
+  while (units.next(S)) {
+    const int kb = units.kb, ke = units.ke;
+    const TilePos tp = tile_pos<BM, BN>(S, M, msplit, units.tile);
+    const int64_t m0 = tp.m0, mlim = tp.mlim, n0 = tp.n0, grp = tp.grp;
+    const float *a0, *a1;
+    if constexpr (AK) {
+      a0 = A.p0 + grp * A.gs0 + m0 * A.ld;
+      a1 = A.p1 + grp * A.gs1 + m0 * A.ld;
+    } else {
+      a0 = a1 = tp.second ? A.p1 + grp * A.gs1 + (m0 - msplit) : A.p0 + grp * A.gs0 + m0;
+    }
+    const float* b0 = B.p0 + grp * B.gs0 + (BK ? n0 * B.ld : n0);
+    const unsigned lda4 = static_cast<unsigned>(A.ld * 4), ldb4 = static_cast<unsigned>(B.ld * 4);
+    sa.init(A.ld, static_cast<int>(min<int64_t>(BM, mlim - m0)), t);
+    sb.init(B.ld, static_cast<int>(min<int64_t>(BN, N - n0)), t);
+    constexpr int NIT = SA::NI + SB::NI;
+    struct Src { const char *a, *b; int klim; };
+    auto src = [&](int j) {
+      int64_t k0;
+      int klim;
+      bool second;
+      k_step<KB>(S, K, ksplit, j, k0, klim, second);
+      return Src{reinterpret_cast<const char*>(AK ? (second ? a1 + (k0 - ksplit) : a0 + k0) : a0 + k0 * A.ld),
+                 reinterpret_cast<const char*>(BK ? b0 + k0 : b0 + k0 * B.ld), klim};
+    };
+    auto src_full = [&](int j) {
+      const bool second = j >= S.nf0;
+      const int64_t k0 = static_cast<int64_t>(second ? j - S.nf0 : j) * KB + (second ? ksplit : 0);
+      return Src{reinterpret_cast<const char*>(AK ? (second ? a1 + (k0 - ksplit) : a0 + k0) : a0 + k0 * A.ld),
+                 reinterpret_cast<const char*>(BK ? b0 + k0 : b0 + k0 * B.ld), KB};
+    };
+    auto load = [&](auto edge, int i, const Src& q) {
+      constexpr bool E = decltype(edge)::value;
+      if (i < SA::NI) sa.template load<E>(i, q.a, lda4, q.klim, t);
+      else sb.template load<E>(i - SA::NI, q.b, ldb4, q.klim, t);
+    };
+    auto stage = [&](auto edge, int buf, int i, int klim) {
+      constexpr bool E = decltype(edge)::value;
+      if (i < SA::NI) {
+#pragma unroll
+        for (int g = 0; g < SA::GP; ++g) sa.template store<E, false>(lds[buf], i * SA::GP + g, klim, 1.f, t);
+      } else {
+#pragma unroll
+        for (int g = 0; g < SB::GP; ++g)
+          sb.template store<E, false>(lds[buf] + 2 * CA, (i - SA::NI) * SB::GP + g, klim, 1.f, t);
+      }
+    };
+    constexpr std::true_type kEdge{};
+    constexpr std::false_type kFull{};
+    bf16x8 av[2][WM], bv[2];   // A's fragments of both halves of a step; B's of this block and the next
+    auto read_a = [&](int buf, int c, int a) {
+      av[c][a] = *reinterpret_cast<const bf16x8*>(lds[buf] + c * CA + (wm * WM + a) * 1024 + (frag ^ chunk_xor(c)));
+    };
+    auto read_b = [&](int buf, int c, int b) {
+      bv[b & 1] = *reinterpret_cast<const bf16x8*>(lds[buf] + 2 * CA + c * CB + (wn * WN + b) * 1024 + (frag ^ chunk_xor(c)));
+    };
+    auto mfmas = [&](int c, int b) {
+#pragma unroll
+      for (int a = 0; a < WM; ++a)
+        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[c][a], bv[b & 1], acc[a][b], 0, 0, 0);
+    };
+    // One step: eight blocks of MFMAs (two halves of K, four block columns).
+    // As in gemm_split_kernel, the items of step j + 2 go to LDS between them
+    // and are at once reloaded with step j + 3, and the last block reads
+    // the next step's first fragments before the barrier.
+    auto step = [&](int cur, int next, int free, int jload) {
+      const Src q = src_full(jload);
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int b = 0; b < WN; ++b) {
+          const int blk = c * WN + b;
+          if (b + 1 < WN) read_b(cur, c, b + 1);
+          else read_b(c == 0 ? cur : next, c ^ 1, 0);
+          if (b == WN - 2) {
+#pragma unroll
+            for (int a = 0; a < WM; ++a) read_a(c == 0 ? cur : next, c ^ 1, a);
+          }
+#pragma unroll
+          for (int i = blk * NIT / (2 * WN); i < (blk + 1) * NIT / (2 * WN); ++i) {
+            stage(kFull, free, i, KB);
+            load(kFull, i, q);
+          }
+          mfmas(c, b);
+#pragma unroll
+          for (int x = 0; x < WM; ++x) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // an MFMA
+            __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);   // some VALU
+            __builtin_amdgcn_sched_group_barrier(0x080, 2, 0);   // LDS accesses
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+#pragma unroll
+    for (int a = 0; a < WM; ++a)
+#pragma unroll
+      for (int b = 0; b < WN; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+    const bool live = wm * WM * 32 < mlim - m0 && wn * WN * 32 < N - n0;
+    lds_barrier();   // the previous tile's LDS is consumed
+    const int fe = min(ke, S.nf);
+    if (kb < fe) {
+      {
+        Src q = src_full(kb);
+#pragma unroll
+        for (int i = 0; i < NIT; ++i) load(kFull, i, q);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          q = src_full(min(kb + s + 1, fe - 1));
+#pragma unroll
+          for (int i = 0; i < NIT; ++i) {
+            stage(kFull, s, i, KB);
+            load(kFull, i, q);
+          }
+        }
+      }
+      lds_barrier();
+      int cur = 0, next = 1, free = 2;
+      if (live) {
+        read_b(0, 0, 0);
+#pragma unroll
+        for (int a = 0; a < WM; ++a) read_a(0, 0, a);
+        for (int j = kb; j < fe; ++j) {
+          step(cur, next, free, min(j + 3, fe - 1));
+          lds_barrier();
+          const int c = cur;
+          cur = next;
+          next = free;
+          free = c;
+        }
+      } else {   // a wave wholly past the matrix only stages
+        for (int j = kb; j < fe; ++j) {
+          const Src q = src_full(min(j + 3, fe - 1));
+#pragma unroll
+          for (int i = 0; i < NIT; ++i) {
+            stage(kFull, free, i, KB);
+            load(kFull, i, q);
+          }
+          lds_barrier();
+          const int c = cur;
+          cur = next;
+          next = free;
+          free = c;
+        }
+      }
+    }
+    for (int j = max(kb, S.nf); j < ke; ++j) {   // the segments' partial steps
+      const Src q = src(j);
+#pragma unroll
+      for (int i = 0; i < NIT; ++i) load(kEdge, i, q);
+#pragma unroll
+      for (int i = 0; i < NIT; ++i) stage(kEdge, 0, i, q.klim);
+      lds_barrier();
+      if (live) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+#pragma unroll
+          for (int a = 0; a < WM; ++a) read_a(0, c, a);
+#pragma unroll
+          for (int b = 0; b < WN; ++b) {
+            read_b(0, c, b);
+            mfmas(c, b);
+          }
+        }
+      }
+      lds_barrier();
+    }
+    if (kb == 0 && ke == S.nk)
+      store_tile<WM, WN>(acc, C, grp, m0 + wm * WM * 32, mlim, n0 + wn * WN * 32, N);
+    else
+      store_part<WM, WN>(acc, 1.f,
                          partials + ((units.tile - S.whole) * S.parts + units.part) * static_cast<int64_t>(BM * BN),
                          wave);
   }
@@ -879,7 +1116,7 @@ struct Cfg {
   double alone_us;    // the least a step takes (memory latency)
   double fixed_us;    // a workgroup's first loads and its stores
 };
-// 0..2: fp32; 3..4: bf16 inputs.  The times were measured with the machine full
+// 0..2: fp32; 3..5: bf16 inputs.  The times were measured with the machine full
 // (256 x 256: 102 steps over 512 tiles in 572 us; 128 x 128: 102 steps over
 // 2,048 tiles in 658; 64 x 64: 8 steps over 2,504 tiles in 112) and nearly
 // empty; choose_cfg takes the shape whose estimate is lowest.  Where two
@@ -890,7 +1127,8 @@ constexpr Cfg kCfg[] = {{256, 256, 16, 1, 8, 256, 2.7, 1.6, 14.0},
                         {128, 128, 16, 2, 8, 256, 1.5, 0.8, 7.0},
                         {64, 64, 64, 3, 2, 64, 3.5, 1.0, 4.0},
                         {128, 128, 64, 2, 2, 1 << 20, 2.0, 1.0, 7.0},
-                        {64, 64, 64, 3, 2, 1 << 20, 1.8, 0.8, 4.0}};
+                        {64, 64, 64, 3, 2, 1 << 20, 1.8, 0.8, 4.0},
+                        {256, 256, 32, 1, 8, 1 << 20, 1.1, 0.9, 14.0}};
 constexpr int64_t kCUs = 256;
 constexpr int64_t kMaxLd = int64_t(1) << 22;   // 255 rows of it in 32 bits of bytes
 
@@ -967,7 +1205,7 @@ SSched make_ssched(int64_t M, int64_t N, int64_t K, int64_t groups, int64_t mspl
 }
 
 int choose_cfg(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups, int64_t msplit, int64_t ksplit) {
-  const int lo = dtype == GIST_DTYPE_BF16_IN ? 3 : 0, hi = dtype == GIST_DTYPE_BF16_IN ? 5 : 3;
+  const int lo = dtype == GIST_DTYPE_BF16_IN ? 3 : 0, hi = dtype == GIST_DTYPE_BF16_IN ? 6 : 3;
   int best = lo;
   double bc = 1e300;
   for (int i = lo; i < hi; ++i) {
@@ -984,16 +1222,14 @@ int64_t sgrid(const SSched& s) {
 
 // Floats per load along the operand's contiguous dimension (4, 2 or 1).
 int vec_of(const Operand& o, int64_t R, int64_t K) {
-  const bool k = o.k_major;
-  const int64_t ext = k ? K : R;
+  const int64_t ext = o.k_major ? K : R;
   const int64_t sp = o.p1 ? o.split : ext;
   for (int v = 4; v > 1; v >>= 1) {
-    if (!k && v == 4) continue;
     const uintptr_t m = 4 * v - 1;
     if (o.ld0 % v == 0 && ext % v == 0 && sp % v == 0 && o.gs0 % v == 0 &&
         !(reinterpret_cast<uintptr_t>(o.p0) & m) &&
         (!o.p1 || (!(reinterpret_cast<uintptr_t>(o.p1) & m) && o.gs1 % v == 0)))
-      return k ? v : 4;
+      return v;
   }
   return 1;
 }
@@ -1003,8 +1239,6 @@ int vec_of(const Operand& o, int64_t R, int64_t K) {
 size_t gemm_workspace(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups, int64_t msplit,
                       int64_t ksplit) {
   if (M <= 0 || N <= 0 || K <= 0 || groups <= 0) return 0;
-  if (dtype == GIST_DTYPE_BF16_IN && gemm_bf16_packed_eligible(M, N, K))
-    return gemm_bf16_packed_workspace(M, N, K);   // groups run one after another
   if (msplit <= 0) msplit = M;
   if (ksplit <= 0) ksplit = K;
   const Cfg& c = kCfg[choose_cfg(M, N, K, dtype, groups, msplit, ksplit)];
@@ -1017,23 +1251,6 @@ gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K, const Operand&
   if (M <= 0 || N <= 0 || groups <= 0) return GIST_OK;
   if (K <= 0) return set_error(GIST_E_UNSUPPORTED, "gemm: K == 0");
   const bool bf = dtype == GIST_DTYPE_BF16_IN;
-  if (bf && gemm_bf16_packed_eligible(M, N, K)) {
-    // the packed path converts each group's operands; groups run in turn
-    for (int64_t g = 0; g < groups; ++g) {
-      Operand ag = A, bg = B;
-      GemmOut cg = C;
-      ag.p0 += g * A.gs0;
-      if (A.p1) ag.p1 += g * A.gs1;
-      bg.p0 += g * B.gs0;
-      if (B.p1) bg.p1 += g * B.gs1;
-      cg.c0 += g * C.gs0;
-      if (C.c1) cg.c1 += g * C.gs1;
-      if (C.mask) cg.mask += g * C.gsm;
-      const gist_status r = gemm_bf16_packed(st, M, N, K, ag, bg, cg, ws, ws_bytes);
-      if (r != GIST_OK) return r;
-    }
-    return GIST_OK;
-  }
   if (K > static_cast<int64_t>(INT32_MAX - 2) * KS)
     return set_error(GIST_E_UNSUPPORTED, "gemm: K too large");
   if ((!A.k_major && B.k_major) || (A.p1 && A.ld1 != A.ld0) || B.p1)
@@ -1043,8 +1260,8 @@ gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K, const Operand&
   int ci = choose_cfg(M, N, K, dtype, groups, msplit, ksplit);
   // 32-bit offsets inside a tile; past them the small kernel, which has 64-bit
   // ones, with whole tiles
-  const bool far = ci < 2 && (A.ld0 >= kMaxLd || B.ld0 >= kMaxLd);
-  if (far) ci = 2;
+  const bool far = (ci < 2 || ci == 5) && (A.ld0 >= kMaxLd || B.ld0 >= kMaxLd);
+  if (far) ci = bf ? 4 : 2;
   const Cfg& c = kCfg[ci];
   SSched s = make_ssched(M, N, K, groups, msplit, ksplit, c, nullptr);
   if (far) {
@@ -1075,12 +1292,13 @@ gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K, const Operand&
 #define GIST_ARGS g, dim3(thr), 0, st, M, N, K, msplit, ksplit, a, b, o, s, part
 #define GIST_SPLIT(AK_, BK_, V_)                                                                             \
   do {                                                                                                       \
-    const unsigned thr = ci == 0 ? 512 : 256;                                                                \
+    const unsigned thr = c.bm == 256 ? 512 : 256;                                                                \
     if (ci == 0) hipLaunchKernelGGL((gemm_split_kernel<2, 4, 4, 2, AK_, BK_, V_>), GIST_ARGS);               \
     else if (ci == 1) hipLaunchKernelGGL((gemm_split_kernel<2, 2, 2, 2, AK_, BK_, V_>), GIST_ARGS);          \
     else if (ci == 2) hipLaunchKernelGGL((gemm_small_kernel<3, 1, 1, AK_, BK_, V_>), GIST_ARGS);             \
     else if (ci == 3) hipLaunchKernelGGL((gemm_small_kernel<1, 2, 2, AK_, BK_, V_>), GIST_ARGS);             \
-    else hipLaunchKernelGGL((gemm_small_kernel<1, 1, 1, AK_, BK_, V_>), GIST_ARGS);                          \
+    else if (ci == 4) hipLaunchKernelGGL((gemm_small_kernel<1, 1, 1, AK_, BK_, V_>), GIST_ARGS);             \
+    else hipLaunchKernelGGL((gemm_bf16_kernel<AK_, BK_, V_>), GIST_ARGS);                                    \
   } while (0)
 #define GIST_SPLIT_V(AK_, BK_)             \
   do {                                     \
@@ -1103,7 +1321,7 @@ gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K, const Operand&
     ProfScope ps(st, "gemm_fixup", 0.0,
                  4.0 * s.ragged * static_cast<double>(c.bm) * c.bn * (s.full + 1.3 * (s.rem > 0) + 1.0));
     const dim3 g(static_cast<unsigned>(s.ragged), static_cast<unsigned>(c.bm * c.bn / 1024));
-    if (ci == 0)
+    if (c.bm == 256)
       hipLaunchKernelGGL((gemm_fixup<2, 4, 4, 2>), g, dim3(256), 0, st, M, N, msplit, s, part, o);
     else if (c.bm == 128)
       hipLaunchKernelGGL((gemm_fixup<2, 2, 2, 2>), g, dim3(256), 0, st, M, N, msplit, s, part, o);
