@@ -15,6 +15,7 @@
 // reproducible.
 
 #include <cstdio>
+#include <type_traits>
 
 #include "common.cuh"
 #include "gist_internal.h"
@@ -59,14 +60,28 @@ __device__ __forceinline__ void store_vec(float* p, const float (&x)[VEC]) {
   *reinterpret_cast<T*>(p) = v;
 }
 
-constexpr int kWaves = 4;  // waves per block
+// Rows with more entries than this are split: a wave's gathers of one row are
+// a serial chain of latencies (eight at a time, about 0.7 us), so a hub row
+// of 1,234 entries alone kept one wave for 109 us on a 20,000-node power-law
+// graph whose other rows took a few (512 columns; now 42 us for the call).
+constexpr int kLongRow = 128;
+
+// Row of slot s (of `slots` in a block): consecutive rows share a block, so
+// that their common neighbours' rows meet in one CU's L1; on sparse graphs
+// (`spread`, at most 16 entries per row on average) there is little to
+// share, and the rows of a block lie rblocks apart, so that the hubs of a
+// degree-ordered graph fall into different blocks.
+__device__ __forceinline__ int64_t row_of(int64_t rblock, int64_t rblocks, int s, int slots, int spread) {
+  return spread ? s * rblocks + rblock : rblock * slots + s;
+}
 
 template <int VEC, int LPR>
 __global__ __launch_bounds__(256) void spmm_kernel(
     int n, const int* __restrict__ rowptr, const int* __restrict__ col,
     const float* __restrict__ val, const float* __restrict__ X, int64_t ldx, int width,
     float* Y, int64_t ldy, const float* add, int64_t ld_add, int relu, int col_tiles,
-    int64_t nblocks, const float* mask, int64_t ldm) {
+    int64_t nblocks, const float* mask, int64_t ldm, int spread) {
+  constexpr int kWaves = 4;
   constexpr int RPW = 64 / LPR;  // rows per wave
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -78,9 +93,10 @@ __global__ __launch_bounds__(256) void spmm_kernel(
   const int64_t rblocks = nblocks / col_tiles;
   const int ctile = static_cast<int>(logical / rblocks);
   const int64_t rblock = logical - static_cast<int64_t>(ctile) * rblocks;
-  const int64_t row = (rblock * kWaves + wave) * RPW + grp;
+  const int64_t row = row_of(rblock, rblocks, wave * RPW + grp, kWaves * RPW, spread);
   const int c0 = ctile * (LPR * VEC) + gl * VEC;
-  const bool active = row < n && c0 < width;
+  const bool incol = c0 < width;
+  const bool active = row < n && incol;
 
   int e0 = 0, e1 = 0;
   if (row < n) {
@@ -101,10 +117,10 @@ __global__ __launch_bounds__(256) void spmm_kernel(
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
 
-  // Walk the row in windows of LPR nonzeros: lane gl of the group loads
-  // nonzero (base + gl), then the group reads them back by shuffle.
-  for (int base = e0; base < e1; base += LPR) {
-    const int cnt = min(LPR, e1 - base);
+  // The entries base .. base + cnt (1 <= cnt <= LPR, the same for the whole
+  // group): lane gl of the group loads one, then the group reads them back by
+  // shuffle, four gathers in flight.
+  auto window = [&](int base, int cnt) {
     int my_c = 0;
     float my_v = 0.f;
     if (gl < cnt) {
@@ -120,7 +136,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(
         cj[u] = __shfl(my_c, grp * LPR + j + u, 64);
         vj[u] = __shfl(my_v, grp * LPR + j + u, 64);
       }
-      if (active) {
+      if (incol) {
         float x[4][VEC];
 #pragma unroll
         for (int u = 0; u < 4; ++u) load_vec<VEC>(X + static_cast<int64_t>(cj[u]) * ldx + c0, x[u]);
@@ -130,14 +146,51 @@ __global__ __launch_bounds__(256) void spmm_kernel(
           for (int v = 0; v < VEC; ++v) acc[v] = fmaf(vj[u], x[u][v], acc[v]);
       }
     }
-    for (; j < cnt; ++j) {
-      const int cj = __shfl(my_c, grp * LPR + j, 64);
-      const float vj = __shfl(my_v, grp * LPR + j, 64);
-      if (active) {
-        float x[VEC];
-        load_vec<VEC>(X + static_cast<int64_t>(cj) * ldx + c0, x);
+    if (j < cnt) {   // the rest together: loads past cnt repeat the last entry, not added
+      int cj[3];
+      float vj[3];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[v] = fmaf(vj, x[v], acc[v]);
+      for (int u = 0; u < 3; ++u) {
+        const int k = grp * LPR + min(j + u, cnt - 1);
+        cj[u] = __shfl(my_c, k, 64);
+        vj[u] = __shfl(my_v, k, 64);
+      }
+      if (incol) {
+        float x[3][VEC];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) load_vec<VEC>(X + static_cast<int64_t>(cj[u]) * ldx + c0, x[u]);
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) acc[v] = j + u < cnt ? fmaf(vj[u], x[u][v], acc[v]) : acc[v];
+      }
+    }
+  };
+  const bool is_long = RPW > 1 && spread && e1 - e0 > kLongRow;
+  {
+    const int end = is_long ? e0 : e1;
+    for (int base = e0; base < end; base += LPR) window(base, min(LPR, end - base));
+  }
+  if (RPW > 1 && spread) {
+    // long rows: the wave's groups take their windows in turn, their sums
+    // are added across the groups
+    unsigned long long todo = __ballot(is_long && gl == 0);
+    while (todo) {
+      const int owner = __ffsll(todo) - 1;
+      todo &= todo - 1;
+      const int l0 = __shfl(e0, owner, 64), l1 = __shfl(e1, owner, 64);
+      float keep[VEC];
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) {
+        keep[v] = acc[v];
+        acc[v] = 0.f;
+      }
+      for (int base = l0 + grp * LPR; base < l1; base += 64) window(base, min(LPR, l1 - base));
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) {
+#pragma unroll
+        for (int o = LPR; o < 64; o <<= 1) acc[v] += __shfl_xor(acc[v], o, 64);
+        if (owner / LPR != grp) acc[v] = keep[v];
       }
     }
   }
@@ -160,14 +213,15 @@ __global__ __launch_bounds__(256) void spmm_kernel(
 // Wide rows (64 lanes per row): the row index is wave-uniform, so each
 // nonzero's (col, val) is broadcast with readlane into scalar registers and
 // the gather address is a scalar base plus the lane's column offset; eight
-// gathers are kept in flight per wave.
-template <int VEC>
-__global__ __launch_bounds__(256) void spmm_wide_kernel(
+// gathers are kept in flight per wave.  A long row's entries are shared by
+// the block's W waves and their sums added in wave order.
+template <int VEC, int W, bool LONG>
+__global__ __launch_bounds__(64 * W) void spmm_wide_kernel(
     int n, const int* __restrict__ rowptr, const int* __restrict__ col,
     const float* __restrict__ val, const float* __restrict__ X, int64_t ldx, int width,
     float* Y, int64_t ldy, const float* add, int64_t ld_add, int relu, int col_tiles,
     int64_t nblocks, const float* mask, int64_t ldm) {
-  constexpr int kUnroll = 8;
+  __shared__ float part[LONG ? W : 1][64 * VEC];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t logical = xcd_remap(blockIdx.x, nblocks);
@@ -176,61 +230,115 @@ __global__ __launch_bounds__(256) void spmm_wide_kernel(
   const int64_t rblocks = nblocks / col_tiles;
   const int ctile = static_cast<int>(logical / rblocks);
   const int64_t rblock = logical - static_cast<int64_t>(ctile) * rblocks;
-  const int64_t row = rblock * kWaves + wave;
-  if (row >= n) return;
+  const int64_t row = row_of(rblock, rblocks, wave, W, LONG);
+  const bool inrow = row < n;
   const int c0 = ctile * (64 * VEC) + lane * VEC;
   const bool active = c0 < width;
-  const int e0 = rowptr[row], e1 = rowptr[row + 1];
-  // Add and mask values load before the gathers (column clamped into the
-  // row: every load is in bounds; an inactive lane's values are never stored)
+  int e0 = 0, e1 = 0;
+  unsigned longs = 0;
+  int s0 = 0, s1 = 0;   // LONG: lane w holds the extent of the block's row w, in every wave,
+                        // so the whole block knows the long ones without a barrier
+  if constexpr (LONG) {
+    const int64_t r = row_of(rblock, rblocks, lane % W, W, LONG);
+    if (r < n) {
+      s0 = rowptr[r];
+      s1 = rowptr[r + 1];
+    }
+    longs = static_cast<unsigned>(__ballot(lane < W && s1 - s0 > kLongRow));
+    if (!(longs >> wave & 1)) {
+      e0 = __builtin_amdgcn_readlane(s0, wave);
+      e1 = __builtin_amdgcn_readlane(s1, wave);
+    }
+  } else if (inrow) {
+    e0 = rowptr[row];
+    e1 = rowptr[row + 1];
+  }
+  // Add and mask values load before the gathers (row and column clamped into
+  // the matrix: every load is in bounds; an inactive lane's values are never stored)
   float a[VEC], mv[VEC];
   {
     const int cc = min(c0, width - VEC);
-    if (add) load_vec<VEC>(add + row * ld_add + cc, a);
-    if (mask) load_vec<VEC>(mask + row * ldm + cc, mv);
+    const int64_t rr = inrow ? row : n - 1;
+    if (add) load_vec<VEC>(add + rr * ld_add + cc, a);
+    if (mask) load_vec<VEC>(mask + rr * ldm + cc, mv);
   }
   const float* Xc = X + c0;
   float acc[VEC];
+  // acc = the sum over entries e0 .. e1
+  auto gather = [&](int e0, int e1) {
 #pragma unroll
-  for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
-  for (int base = e0; base < e1; base += 64) {
-    const int cnt = min(64, e1 - base);
-    int my_c = 0;
-    float my_v = 0.f;
-    if (lane < cnt) {
-      my_c = col[base + lane];
-      my_v = val[base + lane];
-    }
-    int j = 0;
-    for (; j + kUnroll <= cnt; j += kUnroll) {
-      int cj[kUnroll];
-      float vj[kUnroll];
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        cj[u] = __builtin_amdgcn_readlane(my_c, j + u);
-        vj[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), j + u));
+    for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
+    for (int base = e0; base < e1; base += 64) {
+      const int cnt = min(64, e1 - base);
+      int my_c = 0;
+      float my_v = 0.f;
+      if (lane < cnt) {
+        my_c = col[base + lane];
+        my_v = val[base + lane];
       }
-      if (active) {
-        float x[kUnroll][VEC];
+      // U gathers in flight; REST: the loads past cnt repeat its last entry and
+      // are not added
+      auto batch = [&](auto unroll, auto rest, int j) {
+        constexpr int U = decltype(unroll)::value;
+        constexpr bool REST = decltype(rest)::value;
+        int cj[U];
+        float vj[U];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) load_vec<VEC>(Xc + static_cast<int64_t>(cj[u]) * ldx, x[u]);
+        for (int u = 0; u < U; ++u) {
+          const int k = REST ? min(j + u, cnt - 1) : j + u;
+          cj[u] = __builtin_amdgcn_readlane(my_c, k);
+          vj[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), k));
+        }
+        if (active) {
+          float x[U][VEC];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u)
+          for (int u = 0; u < U; ++u) load_vec<VEC>(Xc + static_cast<int64_t>(cj[u]) * ldx, x[u]);
 #pragma unroll
-          for (int v = 0; v < VEC; ++v) acc[v] = fmaf(vj[u], x[u][v], acc[v]);
+          for (int u = 0; u < U; ++u)
+            if (!REST || j + u < cnt) {
+#pragma unroll
+              for (int v = 0; v < VEC; ++v) acc[v] = fmaf(vj[u], x[u][v], acc[v]);
+            }
+        }
+      };
+      int j = 0;
+      for (; j + 8 <= cnt; j += 8) batch(std::integral_constant<int, 8>{}, std::false_type{}, j);
+      if (j + 4 <= cnt) {
+        batch(std::integral_constant<int, 4>{}, std::false_type{}, j);
+        j += 4;
       }
+      if (j < cnt) batch(std::integral_constant<int, 3>{}, std::true_type{}, j);
     }
-    for (; j < cnt; ++j) {
-      const int cj = __builtin_amdgcn_readlane(my_c, j);
-      const float vj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), j));
-      if (active) {
-        float x[VEC];
-        load_vec<VEC>(Xc + static_cast<int64_t>(cj) * ldx, x);
+  };
+  gather(e0, e1);
+  if (LONG && longs) {
+    float keep[VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[v] = fmaf(vj, x[v], acc[v]);
+    for (int v = 0; v < VEC; ++v) keep[v] = acc[v];
+    for (int w = 0; w < W; ++w) {
+      if (!(longs >> w & 1)) continue;
+      const int r0 = __builtin_amdgcn_readlane(s0, w), r1 = __builtin_amdgcn_readlane(s1, w);
+      const int seg = ((r1 - r0 + 8 * W - 1) / (8 * W)) * 8;   // whole batches per wave
+      const int b = min(r0 + wave * seg, r1);
+      gather(b, min(b + seg, r1));
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) part[LONG ? wave : 0][lane * VEC + v] = acc[v];
+      __syncthreads();
+      if (wave == w) {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+          float sum = part[0][lane * VEC + v];
+#pragma unroll
+          for (int q = 1; q < W; ++q) sum += part[LONG ? q : 0][lane * VEC + v];
+          keep[v] = sum;
+        }
       }
+      __syncthreads();
     }
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] = keep[v];
   }
+  if (!inrow) return;
   if (!active) return;
   if (add) {
 #pragma unroll
@@ -252,9 +360,13 @@ gist_status launch(hipStream_t st, int64_t n, int64_t nnz, const int32_t* rowptr
                    const float* val, const float* X, int64_t ldx, int width, float* Y,
                    int64_t ldy, const float* add, int64_t ld_add, bool relu, const float* mask,
                    int64_t ldm) {
+  // sparse matrices: rows spread over the blocks, and (wide rows) eight waves
+  // per block to share a hub
+  const int spread = nnz <= 16 * n ? 1 : 0;
+  const int waves = LPR == 64 && spread ? 8 : 4;
   constexpr int RPW = 64 / LPR;
   const int col_tiles = (width + LPR * VEC - 1) / (LPR * VEC);
-  const int64_t rblocks = (n + kWaves * RPW - 1) / (kWaves * RPW);
+  const int64_t rblocks = (n + waves * RPW - 1) / (waves * RPW);
   const int64_t nblocks = rblocks * col_tiles;
   if (nblocks > INT32_MAX) return set_error(GIST_E_UNSUPPORTED, "spmm: grid too large");
   char name[32];
@@ -266,13 +378,18 @@ gist_status launch(hipStream_t st, int64_t n, int64_t nnz, const int32_t* rowptr
                                                                 (mask ? 1.0 : 0.0));
   ProfScope ps(st, name, 2.0 * static_cast<double>(nnz) * width, bytes);
   if constexpr (LPR == 64) {
-    hipLaunchKernelGGL((spmm_wide_kernel<VEC>), dim3(static_cast<unsigned>(nblocks)), dim3(256),
-                       0, st, static_cast<int>(n), rowptr, col, val, X, ldx, width, Y, ldy, add,
-                       ld_add, relu ? 1 : 0, col_tiles, nblocks, mask, ldm);
+    if (spread)
+      hipLaunchKernelGGL((spmm_wide_kernel<VEC, 8, true>), dim3(static_cast<unsigned>(nblocks)), dim3(512),
+                         0, st, static_cast<int>(n), rowptr, col, val, X, ldx, width, Y, ldy, add,
+                         ld_add, relu ? 1 : 0, col_tiles, nblocks, mask, ldm);
+    else
+      hipLaunchKernelGGL((spmm_wide_kernel<VEC, 4, false>), dim3(static_cast<unsigned>(nblocks)), dim3(256),
+                         0, st, static_cast<int>(n), rowptr, col, val, X, ldx, width, Y, ldy, add,
+                         ld_add, relu ? 1 : 0, col_tiles, nblocks, mask, ldm);
   } else {
     hipLaunchKernelGGL((spmm_kernel<VEC, LPR>), dim3(static_cast<unsigned>(nblocks)), dim3(256),
                        0, st, static_cast<int>(n), rowptr, col, val, X, ldx, width, Y, ldy, add,
-                       ld_add, relu ? 1 : 0, col_tiles, nblocks, mask, ldm);
+                       ld_add, relu ? 1 : 0, col_tiles, nblocks, mask, ldm, spread);
   }
   return check_launch("spmm");
 }
