@@ -702,22 +702,19 @@ extern "C" gist_status gist_gat_layer_bwd(gist_ctx* ctx, const gist_gat_desc* D,
   float* part = reinterpret_cast<float*>(take(p.gemv));
   void* gws = c;
   const float* dZ = dH_out;
-  if (relu) {
-    GIST_TRY(gist::relu_mask(st, n * so, dH_out, H_out, dZbuf));
-    dZ = dZbuf;
-  }
   const int s = static_cast<int>(so);
-  GIST_TRY(gist::gat_scores(st, n, s, P_save, so, a_src, a_dst, u, v));
+  if (relu) dZ = dZbuf;
+  GIST_TRY(gist::gat_bwd_begin(st, n, D->nnz, s, P_save, so, a_src, a_dst, u, v, dH_out, H_out,
+                               relu ? dZbuf : nullptr, A->rowptr, A->col,
+                               D->flags & GIST_GAT_MIRROR_IN_WS ? nullptr : tpos));
   GIST_TRY(gist::gat_edge_grad(st, n, D->nnz, s, A->rowptr, A->col, alpha_save, dZ, so, P_save, so,
                                u, v, D->slope, dpre, du));
-  if (!(D->flags & GIST_GAT_MIRROR_IN_WS))
-    GIST_TRY(gist::gat_mirror(st, n, D->nnz, A->rowptr, A->col, tpos));
   GIST_TRY(gist::gat_mirror_sums(st, n, D->nnz, A->rowptr, tpos, dpre, alpha_save, dv, alpha_t));
   // dP = A_alpha^T dZ (the pattern is symmetric: row j lists the i with alpha_ij)
   GIST_TRY(gist::spmm(st, n, D->nnz, A->rowptr, A->col, alpha_t, dZ, so, s, dP, so, nullptr, 0,
                       false));
-  GIST_TRY(gist::gat_gemv_t(st, n, s, P_save, so, du, dv, da_src, da_dst, part));
-  GIST_TRY(gist::gat_rank2(st, n, s, dP, so, du, dv, a_src, a_dst));
+  // da_src = P^T du, da_dst = P^T dv; dP += du a_src^T + dv a_dst^T
+  GIST_TRY(gist::gat_gemv_t(st, n, s, P_save, so, du, dv, a_src, a_dst, dP, so, da_src, da_dst, part));
   // dW = H^T dP; dH = dP W^T
   gist::Operand a;
   a.p0 = H; a.ld0 = si; a.k_major = false;

@@ -20,17 +20,54 @@ constexpr int kBlock = 256;
 
 __device__ __forceinline__ float leaky(float x, float slope) { return x > 0.f ? x : slope * x; }
 
-// u_i = P_i . a_src, v_i = P_i . a_dst: one wave per row.
-__global__ __launch_bounds__(kBlock) void gat_scores_kernel(int64_t n, int s, const float* __restrict__ P,
-                                                            int64_t ldp, const float* __restrict__ a_src,
-                                                            const float* __restrict__ a_dst,
-                                                            float* __restrict__ u, float* __restrict__ v) {
+// tpos[q] = p where entry q of row j is (j, i) and entry p of row i is
+// (i, j): the position of each entry's mirror in a symmetric pattern, -1
+// where there is none (one wave per row j, binary search in row i; every
+// entry is written, so nothing needs clearing first).
+__device__ __forceinline__ void mirror_row(int64_t j, const int* __restrict__ rowptr,
+                                           const int* __restrict__ col, int* __restrict__ tpos) {
+  const int e1 = rowptr[j + 1];
+  const int jj = static_cast<int>(j);
+  for (int q = rowptr[j] + (threadIdx.x & 63); q < e1; q += 64) {
+    const int i = col[q];
+    const int end = rowptr[i + 1];
+    int lo = rowptr[i], hi = end;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (col[mid] < jj) lo = mid + 1; else hi = mid;
+    }
+    tpos[q] = lo < end && col[lo] == jj ? lo : -1;
+  }
+}
+
+// u_i = P_i . a_src, v_i = P_i . a_dst: one wave per row.  A backward pass
+// also has its other inputs prepared in this launch: dZ = dH * 1[Hout > 0]
+// (dZ not null; all three of row length s) and, in the second half of the
+// grid (tpos not null), the mirror map, which depends on nothing else here.
+// All of it is latency: as four launches (mask, scores, a fill of tpos, map)
+// it took 21 us at 3,100 rows of 45 entries and 256 features, as one 7.8 us.
+__global__ __launch_bounds__(kBlock) void gat_scores_kernel(
+    int64_t n, int s, const float* __restrict__ P, int64_t ldp, const float* __restrict__ a_src,
+    const float* __restrict__ a_dst, float* __restrict__ u, float* __restrict__ v,
+    const float* __restrict__ dH, const float* __restrict__ Hout, float* __restrict__ dZ,
+    unsigned score_blocks, const int* __restrict__ rowptr, const int* __restrict__ col,
+    int* __restrict__ tpos) {
   const int lane = threadIdx.x & 63;
-  const int64_t i = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) >> 6;
+  const bool mirror = blockIdx.x >= score_blocks;
+  const unsigned block = mirror ? blockIdx.x - score_blocks : blockIdx.x;
+  const int64_t i = (static_cast<int64_t>(block) * kBlock + threadIdx.x) >> 6;
   if (i >= n) return;
+  if (mirror) {
+    mirror_row(i, rowptr, col, tpos);
+    return;
+  }
   const float* p = P + i * ldp;
   float su = 0.f, sv = 0.f;
   for (int k = lane; k < s; k += 64) {
+    if (dZ) {
+      const int64_t e = i * s + k;
+      dZ[e] = Hout[e] > 0.f ? dH[e] : 0.f;
+    }
     su = fmaf(p[k], a_src[k], su);
     sv = fmaf(p[k], a_dst[k], sv);
   }
@@ -112,7 +149,13 @@ __device__ __forceinline__ float group_dot(const float* __restrict__ a, const fl
   return part;    // every lane of the group holds the group's sum
 }
 
-template <int VEC>
+// KEEP (VEC 4, s <= 16 G): this lane's features of dZ_i (at most four float4)
+// stay in registers, and the loads of kRowsU entries per group are in flight
+// together; the same products in the same order as group_dot<4>.  The row
+// walk is bound by the latency of col -> P (3,100 rows are 3 waves per SIMD):
+// 256 features, 45 entries per row, 3,100 rows: 30.5 -> 16.7 us.
+constexpr int kRowsU = 4;
+template <int VEC, bool KEEP>
 __global__ __launch_bounds__(kBlock) void gat_edge_grad_kernel(
     int64_t n, int s, int G, const int* __restrict__ rowptr, const int* __restrict__ col,
     const float* __restrict__ alpha, const float* __restrict__ dZ, int64_t ldz,
@@ -131,14 +174,58 @@ __global__ __launch_bounds__(kBlock) void gat_edge_grad_kernel(
   float* keep = keep_lds[wave];
   // pass 1: dalpha of every entry, c_i
   float cpart = 0.f;
-  for (int b = 0; b < len; b += E) {
-    const int q = b + gi;
-    const bool valid = q < len;
-    const int p = e0 + (valid ? q : 0);
-    const float da = group_dot<VEC>(dz, P + static_cast<int64_t>(col[p]) * ldp, s, gl, G);
-    if (valid && gl == 0) {
-      if (q < kKeep) keep[q] = da;
-      cpart = fmaf(alpha[p], da, cpart);
+  if constexpr (KEEP) {
+    float4 x[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const int k = (h * G + gl) * 4;
+      x[h] = k < s ? *reinterpret_cast<const float4*>(dz + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    for (int b = 0; b < len; b += kRowsU * E) {
+      float4 y[kRowsU][4];
+      float al[kRowsU];
+#pragma unroll
+      for (int r = 0; r < kRowsU; ++r) {
+        const int q = b + r * E + gi;
+        const int p = e0 + (q < len ? q : 0);
+        const float* pj = P + static_cast<int64_t>(col[p]) * ldp;
+        al[r] = alpha[p];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+          const int k = (h * G + gl) * 4;
+          y[r][h] = *reinterpret_cast<const float4*>(pj + (k < s ? k : 0));
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < kRowsU; ++r) {
+        const int q = b + r * E + gi;
+        float da = 0.f;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+          if ((h * G + gl) * 4 < s) {
+            da = fmaf(x[h].x, y[r][h].x, da);
+            da = fmaf(x[h].y, y[r][h].y, da);
+            da = fmaf(x[h].z, y[r][h].z, da);
+            da = fmaf(x[h].w, y[r][h].w, da);
+          }
+        }
+        for (int off = G >> 1; off > 0; off >>= 1) da += __shfl_xor(da, off);
+        if (q < len && gl == 0) {
+          if (q < kKeep) keep[q] = da;
+          cpart = fmaf(al[r], da, cpart);
+        }
+      }
+    }
+  } else {
+    for (int b = 0; b < len; b += E) {
+      const int q = b + gi;
+      const bool valid = q < len;
+      const int p = e0 + (valid ? q : 0);
+      const float da = group_dot<VEC>(dz, P + static_cast<int64_t>(col[p]) * ldp, s, gl, G);
+      if (valid && gl == 0) {
+        if (q < kKeep) keep[q] = da;
+        cpart = fmaf(alpha[p], da, cpart);
+      }
     }
   }
   const float c = wave_sum(cpart);
@@ -174,29 +261,6 @@ __global__ __launch_bounds__(kBlock) void gat_edge_grad_kernel(
   if (active && lane == 0) du[i] = npos <= nneg ? (1.f - slope) * tpos : -((1.f - slope) * tneg);
 }
 
-// tpos[q] = p where entry q of row j is (j, i) and entry p of row i is
-// (i, j): the position of each entry's mirror in a symmetric pattern (one
-// wave per row i, binary search in row j).  Mirrors that do not exist keep
-// the -1 the caller filled in.
-__global__ __launch_bounds__(kBlock) void gat_mirror_kernel(int64_t n, const int* __restrict__ rowptr,
-                                                            const int* __restrict__ col,
-                                                            int* __restrict__ tpos) {
-  const int lane = threadIdx.x & 63;
-  const int64_t i = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) >> 6;
-  if (i >= n) return;
-  const int e0 = rowptr[i], e1 = rowptr[i + 1];
-  const int ii = static_cast<int>(i);
-  for (int p = e0 + lane; p < e1; p += 64) {
-    const int j = col[p];
-    int lo = rowptr[j], hi = rowptr[j + 1];
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (col[mid] < ii) lo = mid + 1; else hi = mid;
-    }
-    if (lo < rowptr[j + 1] && col[lo] == ii) tpos[lo] = p;
-  }
-}
-
 // dv_j = sum over row j's entries q of dpre[tpos[q]]; alpha_t[q] =
 // alpha[tpos[q]] (the transposed attention in row j's order).  One wave per
 // row, entries in chunks of 64.
@@ -224,27 +288,14 @@ __global__ __launch_bounds__(kBlock) void gat_mirror_sums_kernel(int64_t n, cons
   if (lane == 0) dv[j] = sum;
 }
 
-// dP_ik += du_i a_src_k + dv_i a_dst_k.
-__global__ __launch_bounds__(kBlock) void gat_rank2_kernel(int64_t n, int s, float* __restrict__ dP,
-                                                           int64_t ld, const float* __restrict__ du,
-                                                           const float* __restrict__ dv,
-                                                           const float* __restrict__ a_src,
-                                                           const float* __restrict__ a_dst) {
-  const int64_t total = n * s;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  for (int64_t e = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x; e < total; e += stride) {
-    const int64_t i = e / s;
-    const int k = static_cast<int>(e - i * s);
-    float* d = dP + i * ld + k;
-    *d = fmaf(dv[i], a_dst[k], fmaf(du[i], a_src[k], *d));
-  }
-}
-
 // da_src = P^T du, da_dst = P^T dv in two deterministic stages.  Stage 1:
 // one block per (64-column group, chunk of rows); wave w sums rows
 // r0 + w, r0 + w + 4, ... of the chunk (lane = column), then the four wave
 // sums are added in wave order.  Stage 2: per column, the chunk sums in
 // chunk order.  At most kMaxChunks chunks, each a multiple of 4 rows.
+// Stage 1 visits every (row, column) once and so also applies the scores'
+// part of dP, dP_ik += du_i a_src_k + dv_i a_dst_k (3,100 x 256: 11.1 us as two
+// launches, 6.8 as one).
 constexpr int kMaxChunks = 1024;
 
 __host__ __device__ inline int64_t gemv_rows_per_chunk(int64_t n) {
@@ -257,6 +308,9 @@ __global__ __launch_bounds__(kBlock) void gat_gemv_partial_kernel(int64_t n, int
                                                                   const float* __restrict__ P,
                                                                   int64_t ldp, const float* __restrict__ du,
                                                                   const float* __restrict__ dv,
+                                                                  const float* __restrict__ a_src,
+                                                                  const float* __restrict__ a_dst,
+                                                                  float* __restrict__ dP, int64_t ldd,
                                                                   float* __restrict__ part) {
   __shared__ float red[2][kWaves][64];
   const int lane = threadIdx.x & 63;
@@ -267,10 +321,14 @@ __global__ __launch_bounds__(kBlock) void gat_gemv_partial_kernel(int64_t n, int
   const int64_t r1 = min<int64_t>(n, r0 + rpc);
   float a = 0.f, b = 0.f;
   if (k < s) {
+    const float as = a_src[k], ad = a_dst[k];
+#pragma unroll 4
     for (int64_t r = r0 + wave; r < r1; r += kWaves) {
-      const float x = P[r * ldp + k];
-      a = fmaf(x, du[r], a);
-      b = fmaf(x, dv[r], b);
+      const float x = P[r * ldp + k], p = du[r], q = dv[r];
+      float* d = dP + r * ldd + k;
+      *d = fmaf(q, ad, fmaf(p, as, *d));
+      a = fmaf(x, p, a);
+      b = fmaf(x, q, b);
     }
   }
   red[0][wave][lane] = a;
@@ -304,25 +362,30 @@ __global__ __launch_bounds__(kBlock) void gat_gemv_final_kernel(int64_t chunks, 
   da_dst[k] = b;
 }
 
-__global__ __launch_bounds__(kBlock) void fill_int_kernel(int* p, int64_t count, int value) {
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  for (int64_t e = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x; e < count; e += stride)
-    p[e] = value;
-}
-
 unsigned rows_grid(int64_t n) { return static_cast<unsigned>((n * 64 + kBlock - 1) / kBlock); }
-unsigned flat_grid(int64_t count) {
-  return static_cast<unsigned>(std::min<int64_t>((count + kBlock - 1) / kBlock, 8192));
-}
 
 }  // namespace
 
 gist_status gat_scores(hipStream_t st, int64_t n, int s, const float* P, int64_t ldp,
                        const float* a_src, const float* a_dst, float* u, float* v) {
   ProfScope ps(st, "gat_scores", 4.0 * n * s, 4.0 * (static_cast<double>(n) * s + 2 * s + 2 * n));
-  hipLaunchKernelGGL(gat_scores_kernel, dim3(rows_grid(n)), dim3(kBlock), 0, st, n, s, P, ldp,
-                     a_src, a_dst, u, v);
+  const unsigned g = rows_grid(n);
+  hipLaunchKernelGGL(gat_scores_kernel, dim3(g), dim3(kBlock), 0, st, n, s, P, ldp, a_src, a_dst, u,
+                     v, nullptr, nullptr, nullptr, g, nullptr, nullptr, nullptr);
   return check_launch("gat_scores");
+}
+
+gist_status gat_bwd_begin(hipStream_t st, int64_t n, int64_t nnz, int s, const float* P, int64_t ldp,
+                          const float* a_src, const float* a_dst, float* u, float* v,
+                          const float* dH, const float* Hout, float* dZ, const int* rowptr,
+                          const int* col, int* tpos) {
+  const double nd = static_cast<double>(n);
+  ProfScope ps(st, "gat_bwd_begin", 4.0 * nd * s,
+               4.0 * ((dZ ? 4.0 : 1.0) * nd * s + 2 * s + 2 * nd) + (tpos ? 12.0 * nnz : 0.0));
+  const unsigned g = rows_grid(n);
+  hipLaunchKernelGGL(gat_scores_kernel, dim3(tpos ? 2 * g : g), dim3(kBlock), 0, st, n, s, P, ldp,
+                     a_src, a_dst, u, v, dH, Hout, dZ, g, rowptr, col, tpos);
+  return check_launch("gat_bwd_begin");
 }
 
 gist_status gat_softmax(hipStream_t st, int64_t n, int64_t nnz, const int* rowptr, const int* col,
@@ -344,23 +407,16 @@ gist_status gat_edge_grad(hipStream_t st, int64_t n, int64_t nnz, int s, const i
                    reinterpret_cast<uintptr_t>(dZ) % 16 == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0;
   int G = 1;
   while (G < 64 && G * 16 < s) G <<= 1;
-  if (vec)
-    hipLaunchKernelGGL(gat_edge_grad_kernel<4>, dim3(rows_grid(n)), dim3(kBlock), 0, st, n, s, G,
+  if (vec && s <= 16 * G)
+    hipLaunchKernelGGL((gat_edge_grad_kernel<4, true>), dim3(rows_grid(n)), dim3(kBlock), 0, st, n, s, G,
+                       rowptr, col, alpha, dZ, ldz, P, ldp, u, v, slope, dpre, du);
+  else if (vec)
+    hipLaunchKernelGGL((gat_edge_grad_kernel<4, false>), dim3(rows_grid(n)), dim3(kBlock), 0, st, n, s, G,
                        rowptr, col, alpha, dZ, ldz, P, ldp, u, v, slope, dpre, du);
   else
-    hipLaunchKernelGGL(gat_edge_grad_kernel<1>, dim3(rows_grid(n)), dim3(kBlock), 0, st, n, s, G,
+    hipLaunchKernelGGL((gat_edge_grad_kernel<1, false>), dim3(rows_grid(n)), dim3(kBlock), 0, st, n, s, G,
                        rowptr, col, alpha, dZ, ldz, P, ldp, u, v, slope, dpre, du);
   return check_launch("gat_edge_grad");
-}
-
-gist_status gat_mirror(hipStream_t st, int64_t n, int64_t nnz, const int* rowptr, const int* col,
-                       int* tpos) {
-  ProfScope ps(st, "gat_mirror", 0.0, 12.0 * nnz);
-  if (nnz > 0)
-    hipLaunchKernelGGL(fill_int_kernel, dim3(flat_grid(nnz)), dim3(kBlock), 0, st, tpos, nnz, -1);
-  hipLaunchKernelGGL(gat_mirror_kernel, dim3(rows_grid(n)), dim3(kBlock), 0, st, n, rowptr, col,
-                     tpos);
-  return check_launch("gat_mirror");
 }
 
 gist_status gat_mirror_sums(hipStream_t st, int64_t n, int64_t nnz, const int* rowptr, const int* tpos,
@@ -371,14 +427,6 @@ gist_status gat_mirror_sums(hipStream_t st, int64_t n, int64_t nnz, const int* r
   return check_launch("gat_mirror_sums");
 }
 
-gist_status gat_rank2(hipStream_t st, int64_t n, int s, float* dP, int64_t ld, const float* du,
-                      const float* dv, const float* a_src, const float* a_dst) {
-  ProfScope ps(st, "gat_rank2", 4.0 * n * s, 8.0 * static_cast<double>(n) * s);
-  hipLaunchKernelGGL(gat_rank2_kernel, dim3(flat_grid(n * s)), dim3(kBlock), 0, st, n, s, dP, ld,
-                     du, dv, a_src, a_dst);
-  return check_launch("gat_rank2");
-}
-
 size_t gat_gemv_workspace(int64_t n, int s) {
   const int64_t rpc = gemv_rows_per_chunk(n);
   const int64_t chunks = (n + rpc - 1) / rpc;
@@ -386,13 +434,14 @@ size_t gat_gemv_workspace(int64_t n, int s) {
 }
 
 gist_status gat_gemv_t(hipStream_t st, int64_t n, int s, const float* P, int64_t ldp, const float* du,
-                       const float* dv, float* da_src, float* da_dst, float* part) {
+                       const float* dv, const float* a_src, const float* a_dst, float* dP, int64_t ldd,
+                       float* da_src, float* da_dst, float* part) {
   const int64_t rpc = gemv_rows_per_chunk(n);
   const int64_t chunks = (n + rpc - 1) / rpc;
-  ProfScope ps(st, "gat_gemv_t", 4.0 * n * s, 4.0 * static_cast<double>(n) * s);
+  ProfScope ps(st, "gat_gemv_t", 8.0 * n * s, 12.0 * static_cast<double>(n) * s);
   const unsigned cx = static_cast<unsigned>((s + 63) / 64);
   hipLaunchKernelGGL(gat_gemv_partial_kernel, dim3(cx, static_cast<unsigned>(chunks)), dim3(kBlock),
-                     0, st, n, s, rpc, P, ldp, du, dv, part);
+                     0, st, n, s, rpc, P, ldp, du, dv, a_src, a_dst, dP, ldd, part);
   hipLaunchKernelGGL(gat_gemv_final_kernel, dim3(static_cast<unsigned>((s + kBlock - 1) / kBlock)),
                      dim3(kBlock), 0, st, chunks, s, part, da_src, da_dst);
   return check_launch("gat_gemv_t");
