@@ -34,41 +34,38 @@ COPY_BYTES = 16384 * 16384 * 4   # one --copy-calib copy: 1 GiB read, 1 GiB writ
 
 
 def short(name):
-    """`gemm_kernel<true, false, ...>` from a demangled kernel symbol."""
+    """`gemm_small_kernel<3, 1, 1, ...>` from a demangled kernel symbol."""
     m = re.search(r"gist::\(anonymous namespace\)::(\w+)(<[^()]*>)?", name)
     return (m.group(1) + (m.group(2) or "")) if m else name[:60]
 
 
 def variant_symbol(variant):
     """Regex over short kernel names that a library profiler variant launches."""
-    b = lambda s: "true" if s else "false"
-    m = re.fullmatch(r"gemm_(f32|bf16)_([KR])([KR])_([vs])([vs])(_n)?", variant)
+    m = re.fullmatch(r"gemm_(f32|bf16)_([KR])([KR])_(\d+)x\d+_v(\d)(\d)", variant)
     if m:
-        dt, ak, bk, av, bv, nar = m.groups()
-        args = ", ".join([b(ak == "K"), b(bk == "K"), b(av == "v"), b(bv == "v"), b(dt == "bf16"),
-                          b(nar is not None)])
-        return re.escape(f"gemm_kernel<{args}>") + "$"
-    m = re.fullmatch(r"gemm_bf16_direct_([KR])([KR])", variant)
-    if m:
-        ak, bk = m.groups()
-        return re.escape(f"gemm_bf16_direct_kernel<{b(ak == 'K')}, {b(bk == 'K')},")
+        dt, ak, bk, tile, va, vb = m.groups()
+        ops = ", ".join("true" if x == "K" else "false" for x in (ak, bk))
+        small = {("f32", "64"): "3, 1, 1", ("bf16", "128"): "1, 2, 2", ("bf16", "64"): "1, 1, 1"}
+        split = {"256": "2, 4, 4, 2", "128": "2, 2, 2, 2"}
+        if (dt, tile) in small:
+            return re.escape(f"gemm_small_kernel<{small[dt, tile]}, {ops}, {va}, {vb}>") + "$"
+        if dt == "f32":
+            return re.escape(f"gemm_split_kernel<{split[tile]}, {ops}, {va}>") + "$"
+        return re.escape(f"gemm_bf16_kernel<{ops}, {va}>") + "$"
     m = re.fullmatch(r"spmm_v(\d+)_l(\d+)", variant)
     if m:
         v, l = m.groups()
-        return (re.escape(f"spmm_wide_kernel<{v}>") if l == "64"
-                else re.escape(f"spmm_kernel<{v}, {l}>")) + "$"
+        return (re.escape(f"spmm_wide_kernel<{v}, ") if l == "64"
+                else re.escape(f"spmm_kernel<{v}, {l}>") + "$")
     table = {
-        "gemm_bf16_packed": r"gemm_bf16_kernel<", "gemm_bf16_fixup": r"fixup_bf16_kernel",
-        "cvt_bf16_K": r"cvt_bf16_kernel<true,", "cvt_bf16_R": r"cvt_bf16_kernel<false,",
-        "gemm_streamk_fixup": r"streamk_fixup", "subagg_gather_rows": r"subagg_gather_rows_kernel<",
+        "gemm_fixup": r"gemm_fixup<", "subagg_gather_rows": r"subagg_gather_rows_kernel<",
         "spmm_tile": r"spmm_tile_kernel",
         "subagg_gather": r"subagg_gather_kernel<", "gather_slice": r"gather_kernel",
         "subagg_scatter": r"scatter_kernel", "sgd_update": r"sgd_kernel",
         "relu_mask": r"relu_mask_kernel", "subagg_mean": r"subagg_mean_kernel",
         "gat_scores": r"gat_scores_kernel", "gat_softmax": r"gat_softmax_kernel",
-        "gat_edge_grad": r"gat_edge_grad_kernel<", "gat_mirror": r"gat_mirror_kernel",
-        "gat_mirror_sums": r"gat_mirror_sums_kernel", "gat_rank2": r"gat_rank2_kernel",
-        "gat_gemv_t": r"gat_gemv_partial_kernel",
+        "gat_bwd_begin": r"gat_scores_kernel", "gat_edge_grad": r"gat_edge_grad_kernel<",
+        "gat_mirror_sums": r"gat_mirror_sums_kernel", "gat_gemv_t": r"gat_gemv_partial_kernel",
     }
     return "^" + table[variant] if variant in table else None
 
