@@ -383,8 +383,13 @@ gist_status gat_bwd_begin(hipStream_t st, int64_t n, int64_t nnz, int s, const f
   ProfScope ps(st, "gat_bwd_begin", 4.0 * nd * s,
                4.0 * ((dZ ? 4.0 : 1.0) * nd * s + 2 * s + 2 * nd) + (tpos ? 12.0 * nnz : 0.0));
   const unsigned g = rows_grid(n);
-  hipLaunchKernelGGL(gat_scores_kernel, dim3(tpos ? 2 * g : g), dim3(kBlock), 0, st, n, s, P, ldp,
+  // a grid holds fewer than 2^32 threads: beyond 33.5M rows the map has a launch of its own
+  const bool one = tpos && 2 * static_cast<uint64_t>(g) * kBlock <= UINT32_MAX;
+  hipLaunchKernelGGL(gat_scores_kernel, dim3(one ? 2 * g : g), dim3(kBlock), 0, st, n, s, P, ldp,
                      a_src, a_dst, u, v, dH, Hout, dZ, g, rowptr, col, tpos);
+  if (tpos && !one)
+    hipLaunchKernelGGL(gat_scores_kernel, dim3(g), dim3(kBlock), 0, st, n, s, P, ldp, a_src, a_dst,
+                       u, v, nullptr, nullptr, nullptr, 0u, rowptr, col, tpos);
   return check_launch("gat_bwd_begin");
 }
 

@@ -55,3 +55,29 @@ def test_mirror_map_fully_written(G, ctx):  # noqa: F811
         out.append([to_host(t) for t in g])
     for x, y in zip(*out):
         assert np.array_equal(x, y) and np.isfinite(x).all()
+
+
+def test_rows_beyond_one_grid(G, ctx):  # noqa: F811
+    """2^25 + 1 rows: the mirror map no longer fits the scores' launch.  Self
+    loops only, so alpha = 1, dP = dZ, dW = H^T dZ, dH = dZ W^T."""
+    import torch
+    n, s = 2 ** 25 + 1, 4
+    log(f"gat n={n} s={s}")
+    g = torch.Generator(device="cuda").manual_seed(3)
+    r = lambda *d: torch.randn(d, generator=g, device="cuda")   # noqa: E731
+    H, W, a1, a2, dHo = r(n, s), r(s, s), r(s), r(s), r(n, s)
+    val = torch.ones(n, device="cuda")
+    rp, col = (torch.arange(k, dtype=torch.int32, device="cuda") for k in (n + 1, n))
+    A = G.csr_dev(n, n, rp, col, val)
+    desc = G.gat_desc(n, n, s, s, 0, G.GIST_DTYPE_F32, 0.2)
+    ws = torch.full((max(G.gist_gat_workspace_size(desc)),), 255, dtype=torch.uint8, device="cuda")
+    P, Ho, alpha = torch.empty(n, s, device="cuda"), torch.empty(n, s, device="cuda"), torch.empty(n, device="cuda")
+    dW, d1, d2, dH = torch.empty(s, s, device="cuda"), torch.empty(s, device="cuda"), torch.empty(
+        s, device="cuda"), torch.empty(n, s, device="cuda")
+    G.gist_gat_layer_fwd(ctx, desc, A, H, W, a1, a2, P, alpha, Ho, ws)
+    G.gist_gat_layer_bwd(ctx, desc, A, H, P, alpha, Ho, W, a1, a2, dHo, dW, d1, d2, dH, ws)
+    # dW sums n fp32 terms of size 1 to about sqrt(n): partial sums of up to 4,096
+    # terms, then n / 4,096 = 8,192 of them, round by at most 8,192 2^-24 = 5e-4 and,
+    # the errors being random, near sqrt(8,192) 2^-24 = 5e-6 of the sums' size
+    assert relerr(to_host(dW), to_host(H.double().T @ dHo.double())) <= FP32_TOL
+    assert relerr(to_host(dH), to_host((dHo.double() @ W.double().T).float())) <= FP32_TOL
