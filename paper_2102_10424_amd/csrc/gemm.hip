@@ -9,7 +9,8 @@
 // fp32 products, exact to fp32 level: a float has 24 significant bits, so it
 // is the exact sum of three bf16 numbers, hi = bf16(x), mid = bf16(x - hi),
 // lo = bf16(x - hi - mid), each rounded to nearest (both differences are
-// exact).  A product is then
+// exact).  Below 2^-109, lo has fewer bits than it needs: such a value is off
+// by up to 2^-134.  A product is then
 //   a b = hi hi' + hi mid' + mid hi' + hi lo' + mid mid' + lo hi' + (terms
 //   below 2^-25 |a b| each),
 // six bf16 products accumulated in fp32 by v_mfma_f32_32x32x16_bf16.  The
