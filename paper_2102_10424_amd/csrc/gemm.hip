@@ -493,8 +493,8 @@ __device__ __forceinline__ void store_part(const floatx16 (&acc)[WM][WN], float 
 // by eight waves (one workgroup per CU) or 128 x 128 by four (two).  Every
 // K step of 16 is 6 WM WN MFMAs per wave between two barriers; three LDS
 // buffers of 6 bytes per value (144 KB at 256 x 256).  Larger tiles halve the
-// splitting work and LDS traffic per MFMA (95 VALU to 48 MFMAs per wave and
-// step at 256 x 256, twice that at 128 x 128), which is what is left of
+// splitting work and LDS traffic per MFMA (105 VALU for it to 48 MFMAs per wave
+// and step at 256 x 256, twice that at 128 x 128), which is what is left of
 // the power for the matrix cores.
 template <int WM, int WN, int NWM, int NWN, bool AK, bool BK, int V>
 __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
@@ -515,12 +515,16 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
   const int frag = lh * 512 + lds_slot(li, lh) * 16;   // this lane's chunk in a 32-row block
 
   Units units(S);
-  // Where the registers allow it the five small products have accumulators
-  // of their own, added at the end: the large sums then round twice per step
-  // (each instruction adds its two halves of K in turn), not twelve times.
+  // The large sums round as seldom as the registers allow (an instruction adds
+  // its two halves of K in turn, so six in one chain round twelve times a
+  // step, which on half-zero activations was more than the fp32 instruction).
+  // Where they allow it the five small products have accumulators of their
+  // own, added at the end: two roundings per step.  Else a block's products
+  // of one step are summed from zero and added as one: one rounding, for 128
+  // additions per wave and step.  Error of 4,096 cubed on ReLU activations:
+  // 9.4e-7 in one chain, 3.2e-7 so (8.1e-7 on the fp32 instruction), and 578 /
+  // 585 / 571 -> 639 / 636 / 632 us (KK, KR, RR).
   constexpr bool DUAL = WM * WN <= 4;
-  // (Error of a product over K = 1,433: 9.3e-8 against 1.8e-7 with one set, and
-  // 3.1e-7 on the fp32 instruction.)
   floatx16 acc[WM][WN], low[DUAL ? WM : 1][DUAL ? WN : 1];
   SA sa;
   SB sb;
@@ -590,14 +594,34 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
       bv[b & 1][p] = *reinterpret_cast<const bf16x8*>(lds[buf] + ABYTES + (wn * WN + (b % WN)) * 1024 +
                                                       frag + p * plane_bytes<BN>());
     };
-    // The six products of block column b, smallest first; plane p of A is
-    // last used at kLastA[p], so its registers can take the next step's.
+    // The six products of block column b, smallest first.  A's plane 2 is last
+    // used by the first, its plane 1 by the third: `after` may then read the
+    // next step's into those registers.
     constexpr int TA[6] = {2, 1, 1, 0, 0, 0}, TB[6] = {0, 1, 0, 2, 1, 0};
-    auto mfmas = [&](int b, int q) {
+    auto mfmas = [&](int b, auto after) {
+      if constexpr (DUAL) {
 #pragma unroll
-      for (int a = 0; a < WM; ++a) {
-        floatx16& c = DUAL && q < 5 ? low[DUAL ? a : 0][DUAL ? b : 0] : acc[a][b];
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[a][TA[q]], bv[b & 1][TB[q]], c, 0, 0, 0);
+        for (int q = 0; q < 6; ++q) {
+#pragma unroll
+          for (int a = 0; a < WM; ++a) {
+            floatx16& c = q < 5 ? low[a][b] : acc[a][b];
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[a][TA[q]], bv[b & 1][TB[q]], c, 0, 0, 0);
+          }
+#pragma unroll
+          for (int a = 0; a < WM; ++a) after(a, q);
+        }
+      } else {
+        floatx16 c[WM] = {};
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+#pragma unroll
+          for (int a = 0; a < WM; ++a)
+            c[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[a][TA[q]], bv[b & 1][TB[q]], c[a], 0, 0, 0);
+#pragma unroll
+          for (int a = 0; a < WM; ++a) after(a, q);
+        }
+#pragma unroll
+        for (int a = 0; a < WM; ++a) acc[a][b] += c[a];
       }
     };
     // One K step from LDS buffer cur.  Every block of MFMAs also splits some
@@ -619,18 +643,9 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
           stage(kFull, free, i, KS);
           load(kFull, i, src);
         }
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-          mfmas(b, q);
-          if (b == WN - 1 && q == 0) {
-#pragma unroll
-            for (int a = 0; a < WM; ++a) read_a(next, a, 2);
-          }
-          if (b == WN - 1 && q == 2) {
-#pragma unroll
-            for (int a = 0; a < WM; ++a) read_a(next, a, 1);
-          }
-        }
+        mfmas(b, [&](int a, int q) {
+          if (b == WN - 1 && (q == 0 || q == 2)) read_a(next, a, q == 0 ? 2 : 1);
+        });
 #pragma unroll
         for (int q = 0; q < 6 * WM; ++q) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // an MFMA
@@ -719,8 +734,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
         for (int b = 0; b < WN; ++b) {
 #pragma unroll
           for (int p = 0; p < 3; ++p) read_b(0, b, p);
-#pragma unroll
-          for (int q6 = 0; q6 < 6; ++q6) mfmas(b, q6);
+          mfmas(b, [](int, int) {});
         }
       }
       lds_barrier();
@@ -1118,13 +1132,13 @@ struct Cfg {
   double fixed_us;    // a workgroup's first loads and its stores
 };
 // 0..2: fp32; 3..5: bf16 inputs.  The times were measured with the machine full
-// (256 x 256: 102 steps over 512 tiles in 572 us; 128 x 128: 102 steps over
+// (256 x 256: 102 steps over 512 tiles in 630 us; 128 x 128: 102 steps over
 // 2,048 tiles in 658; 64 x 64: 8 steps over 2,504 tiles in 112) and nearly
 // empty; choose_cfg takes the shape whose estimate is lowest.  Where two
 // are close: 3,100 x 1,024 over K = 1,204 takes 72.0 / 72.6 / 89 us with the
 // three fp32 tiles, 1,630 x 8,192 over K = 47 24 / 30 / 42, 2,000 x 128 over
 // K = 1,433 32 / 21 / 23, 3,100 x 64 over K = 602 35 / 21 / 12.
-constexpr Cfg kCfg[] = {{256, 256, 16, 1, 8, 256, 2.7, 1.6, 14.0},
+constexpr Cfg kCfg[] = {{256, 256, 16, 1, 8, 256, 2.95, 1.75, 14.0},
                         {128, 128, 16, 2, 8, 256, 1.5, 0.8, 7.0},
                         {64, 64, 64, 3, 2, 64, 3.5, 1.0, 4.0},
                         {128, 128, 64, 2, 2, 1 << 20, 2.0, 1.0, 7.0},
