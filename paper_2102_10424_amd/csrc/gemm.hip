@@ -9,8 +9,12 @@
 // fp32 products, exact to fp32 level: a float has 24 significant bits, so it
 // is the exact sum of three bf16 numbers, hi = bf16(x), mid = bf16(x - hi),
 // lo = bf16(x - hi - mid), each rounded to nearest (both differences are
-// exact).  Below 2^-109, lo has fewer bits than it needs: such a value is off
-// by up to 2^-134.  A product is then
+// exact).  The last bit of a float can be 2^-149, so both operands are split
+// times 2^24 and the sums divided by 2^48 (both exact): no part is then a
+// subnormal bf16 number.  (Unscaled, values below 2^-109 lost bits, and all of
+// them below 2^-134.  2^16 would keep every bit, but the unit aligns a
+// subnormal's products by its unnormalised exponent, which cost values below
+// 2^-142 up to seven bits.)  A product is then
 //   a b = hi hi' + hi mid' + mid hi' + hi lo' + mid mid' + lo hi' + (terms
 //   below 2^-25 |a b| each),
 // six bf16 products accumulated in fp32 by v_mfma_f32_32x32x16_bf16.  The
@@ -27,11 +31,11 @@
 // dW; back to back, hot) and this 620 / 610 / 600; for 512 x 512 weights
 // and 20,000 nodes 134 -> 83 us; a 1,536 x 64 product over K = 602 27 -> 11.
 //
-// Non-finite values: the split of an Inf or NaN (or of a value that rounds to
-// Inf in bf16) leaves NaN in the tile, so a wave whose accumulators hold
-// anything non-finite recomputes its block with the fp32 matrix instruction
-// straight from memory; finite inputs never take that path unless the
-// product overflows.
+// Non-finite and huge values: the split of an Inf or NaN, or of a value that is
+// Inf in bf16 when scaled (from 2^104 on), leaves NaN in the tile, and sums
+// from 2^80 on overflow; so a wave whose accumulators hold anything non-finite
+// recomputes its block with the fp32 matrix instruction straight from memory.
+// No other input takes that path.
 //
 // bf16-input products round the operands (nearest even) on the same way to LDS
 // and take one product: gemm_bf16_kernel (256 x 256 tiles) and
@@ -84,6 +88,9 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 constexpr int KS = 16;         // K per step: one bf16 MFMA
+
+// Scale of both operands of an fp32 product, and what takes it out of the sums.
+constexpr float kScale = 16777216.f, kUnscale = 1.f / (kScale * kScale);
 
 // Operand view: element (r, k) at p[r * ld + k] (K contiguous) or
 // p[k * ld + r]; p1 takes over at the segment boundary (along K or rows).
@@ -235,9 +242,9 @@ struct Stage {
       }
     }
   }
-  // split group g into the three planes of the LDS tile S (EDGE: K values from
-  // klim on are zero)
-  template <bool EDGE, bool SIGN>
+  // split group g, times sg for fp32 products, into the planes of the LDS tile S
+  // (EDGE: K values from klim on are zero)
+  template <bool EDGE>
   __device__ __forceinline__ void store(char* S, int g, int klim, float sg, int t) const {
     int row, kk;
     item(t, g / GP, row, kk);
@@ -246,7 +253,7 @@ struct Stage {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       x[j] = !EDGE || kk + j < klim ? v[g][j] : 0.f;
-      if (SIGN) x[j] *= sg;
+      if (NP > 1) x[j] *= sg;
     }
     uintx2 pl[NP];
     split4<NP>(x, pl);
@@ -412,9 +419,9 @@ __device__ __forceinline__ void recompute(floatx16 (&acc)[WM][WN], const SSched&
 // One 32 x 32 block to C.  Accumulator register r of lane l: row
 // 8 (r / 4) + 4 (l / 32) + (r mod 4), column l mod 32.  The mask and the
 // weights of a fused SGD step are all read before anything is written.
-// WHOLE: all 32 rows lie in the matrix.
+// WHOLE: all 32 rows lie in the matrix.  f: factor of the accumulators.
 template <bool WHOLE>
-__device__ __forceinline__ void store_block(const floatx16& acc, const SOut& C, int64_t row0, int64_t mlim,
+__device__ __forceinline__ void store_block(const floatx16& acc, float f, const SOut& C, int64_t row0, int64_t mlim,
                                             int64_t col, int64_t N) {
   if (col >= N) return;
   const bool lo = col < C.c_split;
@@ -423,7 +430,7 @@ __device__ __forceinline__ void store_block(const floatx16& acc, const SOut& C, 
   const int left = static_cast<int>(min<int64_t>(mlim - row0, 32));
   float v[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) v[r] = C.relu ? fmaxf(acc[r], 0.f) : acc[r];
+  for (int r = 0; r < 16; ++r) v[r] = C.relu ? fmaxf(f * acc[r], 0.f) : f * acc[r];
   if (C.mask && lo) {
     const float* m = C.mask + row0 * C.ldm + col;
     float k[16];
@@ -454,8 +461,8 @@ __device__ __forceinline__ void store_block(const floatx16& acc, const SOut& C, 
 
 // This wave's block of a tile whose whole K it holds.
 template <int WM, int WN>
-__device__ __forceinline__ void store_tile(const floatx16 (&acc)[WM][WN], const SOut& C, int64_t grp, int64_t row,
-                                           int64_t mlim, int64_t col, int64_t N) {
+__device__ __forceinline__ void store_tile(const floatx16 (&acc)[WM][WN], float f, const SOut& C, int64_t grp,
+                                           int64_t row, int64_t mlim, int64_t col, int64_t N) {
   const int li = threadIdx.x & 31, lh = (threadIdx.x >> 5) & 1;
   SOut Cg = C;
   Cg.c0 += grp * C.gs0;
@@ -466,15 +473,15 @@ __device__ __forceinline__ void store_tile(const floatx16 (&acc)[WM][WN], const 
 #pragma unroll
     for (int b = 0; b < WN; ++b) {
       const int64_t r0 = row + a * 32 + 4 * lh, c = col + b * 32 + li;
-      if (row + a * 32 + 32 <= mlim) store_block<true>(acc[a][b], Cg, r0, mlim, c, N);
-      else store_block<false>(acc[a][b], Cg, r0, mlim, c, N);
+      if (row + a * 32 + 32 <= mlim) store_block<true>(acc[a][b], f, Cg, r0, mlim, c, N);
+      else store_block<false>(acc[a][b], f, Cg, r0, mlim, c, N);
     }
 }
 
 // A partial tile in accumulator order (block, r / 4, lane, r mod 4): 16-byte
 // stores of whole lines.
 template <int WM, int WN>
-__device__ __forceinline__ void store_part(const floatx16 (&acc)[WM][WN], float sg, float* part, int wave) {
+__device__ __forceinline__ void store_part(const floatx16 (&acc)[WM][WN], float f, float* part, int wave) {
   floatx4* dst = reinterpret_cast<floatx4*>(part) + wave * (WM * WN * 256) + (threadIdx.x & 63);
 #pragma unroll
   for (int a = 0; a < WM; ++a)
@@ -484,7 +491,7 @@ __device__ __forceinline__ void store_part(const floatx16 (&acc)[WM][WN], float 
       for (int r4 = 0; r4 < 4; ++r4) {
         floatx4 x;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) x[q] = sg * acc[a][b][4 * r4 + q];
+        for (int q = 0; q < 4; ++q) x[q] = f * acc[a][b][4 * r4 + q];
         dst[((a * WN + b) * 4 + r4) * 64] = x;
       }
 }
@@ -550,7 +557,8 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
     // over a long K: a workgroup takes at most 4,096 values of K, and
     // the parts of a tile take turns at accumulating the product and its
     // negative (A negated on its way to LDS), so that the bias cancels.
-    float sg = units.part & 1 ? -1.f : 1.f;
+    const float sg = units.part & 1 ? -kScale : kScale;
+    float f = units.part & 1 ? -kUnscale : kUnscale;   // takes sign and scale out of the sums
     struct Src { const char *a, *b; int klim; };
     auto src_full = [&](int j) {           // where whole step j is
       const bool second = j >= S.nf0;
@@ -576,11 +584,11 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
       constexpr bool E = decltype(edge)::value;
       if (i < SA::NI) {
 #pragma unroll
-        for (int g = 0; g < SA::GP; ++g) sa.template store<E, true>(lds[buf], i * SA::GP + g, klim, sg, t);
+        for (int g = 0; g < SA::GP; ++g) sa.template store<E>(lds[buf], i * SA::GP + g, klim, sg, t);
       } else {
 #pragma unroll
         for (int g = 0; g < SB::GP; ++g)
-          sb.template store<E, false>(lds[buf] + ABYTES, (i - SA::NI) * SB::GP + g, klim, sg, t);
+          sb.template store<E>(lds[buf] + ABYTES, (i - SA::NI) * SB::GP + g, klim, kScale, t);
       }
     };
     constexpr std::true_type kEdge{};
@@ -747,14 +755,14 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
         for (int b = 0; b < WN; ++b) acc[a][b] += low[a][b];
     }
     if (any_nonfinite<WM, WN>(acc)) {
-      sg = 1.f;
+      f = 1.f;
       recompute<WM, WN, KS, AK, BK>(acc, S, K, ksplit, kb, ke, a0, a1, A.ld, b0, B.ld, wm * WM * 32,
                                     wn * WN * 32, mlim - m0, N - n0);
     }
     if (kb == 0 && ke == S.nk)
-      store_tile<WM, WN>(acc, C, grp, m0 + wm * WM * 32, mlim, n0 + wn * WN * 32, N);
+      store_tile<WM, WN>(acc, f, C, grp, m0 + wm * WM * 32, mlim, n0 + wn * WN * 32, N);
     else
-      store_part<WM, WN>(acc, sg,
+      store_part<WM, WN>(acc, f,
                          partials + ((units.tile - S.whole) * S.parts + units.part) * static_cast<int64_t>(BM * BN),
                          wave);
   }
@@ -814,7 +822,8 @@ __global__ __launch_bounds__(256, WM == 1 ? 3 : 2) void gemm_small_kernel(
       for (int i = 0; i < SB::NI; ++i) sb.template load<true>(i, pb, B.ld * 4, klim, t);
       return klim;
     };
-    float sg = EXACT && (units.part & 1) ? -1.f : 1.f;   // see gemm_split_kernel
+    const float sg = units.part & 1 ? -kScale : kScale;   // sg, f: see gemm_split_kernel
+    float f = !EXACT ? 1.f : units.part & 1 ? -kUnscale : kUnscale;
 #pragma unroll
     for (int a = 0; a < WM; ++a)
 #pragma unroll
@@ -828,9 +837,9 @@ __global__ __launch_bounds__(256, WM == 1 ? 3 : 2) void gemm_small_kernel(
     for (int j = kb; j < ke; ++j) {
       lds_barrier();   // the last step's fragments are read
 #pragma unroll
-      for (int g = 0; g < SA::NG; ++g) sa.template store<true, EXACT>(lds, g, klim, sg, t);
+      for (int g = 0; g < SA::NG; ++g) sa.template store<true>(lds, g, klim, sg, t);
 #pragma unroll
-      for (int g = 0; g < SB::NG; ++g) sb.template store<true, false>(ldsB, g, klim, sg, t);
+      for (int g = 0; g < SB::NG; ++g) sb.template store<true>(ldsB, g, klim, kScale, t);
       if (j + 1 < ke) klim = load(j + 1);
       lds_barrier();
 #pragma unroll
@@ -867,15 +876,15 @@ __global__ __launch_bounds__(256, WM == 1 ? 3 : 2) void gemm_small_kernel(
 #pragma unroll
         for (int b = 0; b < WN; ++b) acc[a][b] += low[a][b];
       if (any_nonfinite<WM, WN>(acc)) {
-        sg = 1.f;
+        f = 1.f;
         recompute<WM, WN, KL, AK, BK>(acc, S, K, ksplit, kb, ke, a0, a1, A.ld, b0, B.ld, wm * WM * 32,
                                       wn * WN * 32, tp.mlim - m0, N - n0);
       }
     }
     if (kb == 0 && ke == S.nk)
-      store_tile<WM, WN>(acc, C, grp, m0 + wm * WM * 32, tp.mlim, n0 + wn * WN * 32, N);
+      store_tile<WM, WN>(acc, f, C, grp, m0 + wm * WM * 32, tp.mlim, n0 + wn * WN * 32, N);
     else
-      store_part<WM, WN>(acc, sg,
+      store_part<WM, WN>(acc, f,
                          partials + ((units.tile - S.whole) * S.parts + units.part) * static_cast<int64_t>(BM * BN),
                          wave);
   }
@@ -951,11 +960,11 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(int64_t M, int64_t N,
       constexpr bool E = decltype(edge)::value;
       if (i < SA::NI) {
 #pragma unroll
-        for (int g = 0; g < SA::GP; ++g) sa.template store<E, false>(lds[buf], i * SA::GP + g, klim, 1.f, t);
+        for (int g = 0; g < SA::GP; ++g) sa.template store<E>(lds[buf], i * SA::GP + g, klim, 1.f, t);
       } else {
 #pragma unroll
         for (int g = 0; g < SB::GP; ++g)
-          sb.template store<E, false>(lds[buf] + 2 * CA, (i - SA::NI) * SB::GP + g, klim, 1.f, t);
+          sb.template store<E>(lds[buf] + 2 * CA, (i - SA::NI) * SB::GP + g, klim, 1.f, t);
       }
     };
     constexpr std::true_type kEdge{};
@@ -1080,7 +1089,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(int64_t M, int64_t N,
       lds_barrier();
     }
     if (kb == 0 && ke == S.nk)
-      store_tile<WM, WN>(acc, C, grp, m0 + wm * WM * 32, mlim, n0 + wn * WN * 32, N);
+      store_tile<WM, WN>(acc, 1.f, C, grp, m0 + wm * WM * 32, mlim, n0 + wn * WN * 32, N);
     else
       store_part<WM, WN>(acc, 1.f,
                          partials + ((units.tile - S.whole) * S.parts + units.part) * static_cast<int64_t>(BM * BN),

@@ -68,3 +68,44 @@ def test_rounding_of_wide_tiles(env):
         rel = _rel(got, a, b)
         print(f"{what}: rel {rel:.2e}", flush=True)
         assert rel < 5e-7, (what, rel)
+
+
+@pytest.mark.parametrize("n,si,so,tile", [(70, 40, 50, 64), (3100, 602, 1024, 128), (4096, 512, 4096, 256)])
+@pytest.mark.parametrize("exp", [-100, -116, -126, -140, -149])
+def test_operands_down_to_the_smallest_subnormal(env, n, si, so, tile, exp):
+    """Operands around 2^exp against ones that bring the results to ordinary size: every bit of a
+    float counts, as with a plain fp32 product (2e-6 holds for K up to 4,096; see
+    test_gpu_gemm_split).  Small values on either side of the product (dW has them on the left,
+    dH with a small dZ too, the forward with a small W on the right)."""
+    torch = env[0]
+    r = _randn(torch, 2)
+    tiny = lambda *s: torch.ldexp(torch.ldexp(r(*s), torch.tensor(exp // 2, device="cuda")),   # noqa: E731
+                                  torch.tensor(exp - exp // 2, device="cuda"))
+    big = lambda *s: r(*s) * 2.0 ** 75   # noqa: E731
+    H, W, dZ = tiny(n, si), big(si, so), big(n, so)
+    assert int(H.count_nonzero()) > 0
+    out, dW, _, names = _gcn(env, H, W, dZ)
+    assert any(f"_{tile}x{tile}_" in k for k in names), names
+    cases = [("H W", out, H, W), ("H^T dZ", dW, H.t(), dZ)]
+    H, W, dZ = big(n, si), tiny(si, so), tiny(n, so)
+    out, dW, _, _ = _gcn(env, H, W, dZ)
+    cases += [("H W, small W", out, H, W), ("H^T dZ, small dZ", dW, H.t(), dZ)]
+    for what, got, a, b in cases:
+        rel = _rel(got, a, b)
+        print(f"2^{exp} {what}: rel {rel:.2e}", flush=True)
+        assert rel < 2e-6, (what, rel)
+
+
+@pytest.mark.parametrize("n,si,so,tile", [(70, 40, 50, 64), (3100, 602, 1024, 128), (4096, 512, 4096, 256)])
+def test_operands_up_to_the_largest(env, n, si, so, tile):
+    """Values and sums near the top of the range, where the scaled parts or their sums overflow."""
+    torch = env[0]
+    r = _randn(torch, 3)
+    for a, b in ((2.0 ** 60, 2.0 ** 40), (2.0 ** 60, 2.0 ** 58), (2.0 ** 111, 1.0), (2.0 ** 118, 2.0 ** -20)):
+        H, W, dZ = r(n, si) * a, r(si, so) * b, r(n, so) * b
+        out, dW, _, names = _gcn(env, H, W, dZ)
+        assert any(f"_{tile}x{tile}_" in k for k in names), names
+        for what, got, x, y in (("H W", out, H, W), ("H^T dZ", dW, H.t(), dZ)):
+            rel = _rel(got, x, y)
+            print(f"{a:.0e} {b:.0e} {what}: rel {rel:.2e}", flush=True)
+            assert rel < 2e-6, (what, rel)
