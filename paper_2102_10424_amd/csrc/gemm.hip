@@ -42,8 +42,8 @@
 // gemm_small_kernel<1, ...>.
 
 // Work distribution: tiles are whole where there are enough of them.  The
-// tiles of the last, partly filled round (or all, where K is beyond 4,096)
-// are cut in K, all at the same steps, slice-major, so that the workgroups an
+// tiles of the last, partly filled round (or all, where K is beyond 4,096 and
+// the parts fit kMaxPartBytes) are cut in K, all at the same steps, slice-major, so that the workgroups an
 // XCD runs together share each K range's operand rows in L2; what is left of
 // each tile is dealt out in runs of the same length.  Partial tiles go to
 // the workspace and a second kernel sums them in K order: deterministic, and
@@ -88,6 +88,7 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 constexpr int KS = 16;         // K per step: one bf16 MFMA
+constexpr int kRunK = 4096;    // values of K accumulated before the sign turns (gemm_split_kernel)
 
 // Scale of both operands of an fp32 product, and what takes it out of the sums.
 constexpr float kScale = 16777216.f, kUnscale = 1.f / (kScale * kScale);
@@ -554,10 +555,10 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
     constexpr int NIT = SA::NI + SB::NI;   // load items per thread, A's first
     // The bf16 unit's sums round a little toward minus infinity (0.003 of a
     // unit in the last place per instruction, on average), which would add up
-    // over a long K: a workgroup takes at most 4,096 values of K, and
-    // the parts of a tile take turns at accumulating the product and its
-    // negative (A negated on its way to LDS), so that the bias cancels.
-    const float sg = units.part & 1 ? -kScale : kScale;
+    // over a long K: every 4,096 values of K, and from one part of a tile to
+    // the next, a workgroup turns from accumulating the product to its negative
+    // or back (A negated on its way to LDS), so that the bias cancels.
+    float sg = units.part & 1 ? -kScale : kScale;
     float f = units.part & 1 ? -kUnscale : kUnscale;   // takes sign and scale out of the sums
     struct Src { const char *a, *b; int klim; };
     auto src_full = [&](int j) {           // where whole step j is
@@ -677,15 +678,27 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
     // a wave wholly past the matrix only stages
     const bool live = wm * WM * 32 < mlim - m0 && wn * WN * 32 < N - n0;
     lds_barrier();   // the previous tile's LDS is consumed
-    const int fe = min(ke, S.nf);
-    if (kb < fe) {
+    const int whole_end = min(ke, S.nf);
+    for (int rb = kb; rb < whole_end; rb += kRunK / KS) {
+      const int fe = min(rb + kRunK / KS, whole_end);
+      if (rb > kb) {
+        sg = -sg;
+        f = -f;
+#pragma unroll
+        for (int a = 0; a < WM; ++a)
+#pragma unroll
+          for (int b = 0; b < WN; ++b) {
+            acc[a][b] = -acc[a][b];
+            if constexpr (DUAL) low[a][b] = -low[a][b];
+          }
+      }
       {
-        Src q = src_full(kb);
+        Src q = src_full(rb);
 #pragma unroll
         for (int i = 0; i < NIT; ++i) load(kFull, i, q);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-          q = src_full(min(kb + s + 1, fe - 1));
+          q = src_full(min(rb + s + 1, fe - 1));
 #pragma unroll
           for (int i = 0; i < NIT; ++i) {
             stage(kFull, s, i, KS);
@@ -702,7 +715,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
 #pragma unroll
           for (int a = 0; a < WM; ++a) read_a(0, a, p);
         }
-        for (int j = kb; j < fe; ++j) {
+        for (int j = rb; j < fe; ++j) {
           step(cur, next, free, min(j + 3, fe - 1));
           lds_barrier();
           const int c = cur;
@@ -711,7 +724,7 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
           free = c;
         }
       } else {
-        for (int j = kb; j < fe; ++j) {
+        for (int j = rb; j < fe; ++j) {
           const Src q = src_full(min(j + 3, fe - 1));
 #pragma unroll
           for (int i = 0; i < NIT; ++i) {
@@ -822,7 +835,7 @@ __global__ __launch_bounds__(256, WM == 1 ? 3 : 2) void gemm_small_kernel(
       for (int i = 0; i < SB::NI; ++i) sb.template load<true>(i, pb, B.ld * 4, klim, t);
       return klim;
     };
-    const float sg = units.part & 1 ? -kScale : kScale;   // sg, f: see gemm_split_kernel
+    float sg = units.part & 1 ? -kScale : kScale;   // sg, f: see gemm_split_kernel
     float f = !EXACT ? 1.f : units.part & 1 ? -kUnscale : kUnscale;
 #pragma unroll
     for (int a = 0; a < WM; ++a)
@@ -835,6 +848,17 @@ __global__ __launch_bounds__(256, WM == 1 ? 3 : 2) void gemm_small_kernel(
         }
     int klim = load(kb);
     for (int j = kb; j < ke; ++j) {
+      if (EXACT && j > kb && (j - kb) % (kRunK / KL) == 0) {
+        sg = -sg;
+        f = -f;
+#pragma unroll
+        for (int a = 0; a < WM; ++a)
+#pragma unroll
+          for (int b = 0; b < WN; ++b) {
+            acc[a][b] = -acc[a][b];
+            if constexpr (EXACT) low[a][b] = -low[a][b];
+          }
+      }
       lds_barrier();   // the last step's fragments are read
 #pragma unroll
       for (int g = 0; g < SA::NG; ++g) sa.template store<true>(lds, g, klim, sg, t);
@@ -1135,7 +1159,7 @@ struct Cfg {
   int bm, bn, kw;     // tile, K per step
   int per_cu;         // workgroups a CU holds at once
   int min_steps;      // fewest steps worth a workgroup of their own
-  int max_run;        // most steps a workgroup accumulates (4,096 values of K)
+  int max_run;        // steps a workgroup accumulates at most, if the parts fit kMaxPartBytes
   double step_us;     // one step of one workgroup with per_cu of them on every CU
   double alone_us;    // the least a step takes (memory latency)
   double fixed_us;    // a workgroup's first loads and its stores
@@ -1147,14 +1171,20 @@ struct Cfg {
 // are close: 3,100 x 1,024 over K = 1,204 takes 72.0 / 72.6 / 89 us with the
 // three fp32 tiles, 1,630 x 8,192 over K = 47 24 / 30 / 42, 2,000 x 128 over
 // K = 1,433 32 / 21 / 23, 3,100 x 64 over K = 602 35 / 21 / 12.
-constexpr Cfg kCfg[] = {{256, 256, 16, 1, 8, 256, 2.95, 1.75, 14.0},
-                        {128, 128, 16, 2, 8, 256, 1.5, 0.8, 7.0},
-                        {64, 64, 64, 3, 2, 64, 3.5, 1.0, 4.0},
+constexpr Cfg kCfg[] = {{256, 256, KS, 1, 8, kRunK / KS, 2.95, 1.75, 14.0},
+                        {128, 128, KS, 2, 8, kRunK / KS, 1.5, 0.8, 7.0},
+                        {64, 64, KL, 3, 2, kRunK / KL, 3.5, 1.0, 4.0},
                         {128, 128, 64, 2, 2, 1 << 20, 2.0, 1.0, 7.0},
                         {64, 64, 64, 3, 2, 1 << 20, 1.8, 0.8, 4.0},
                         {256, 256, 32, 1, 8, 1 << 20, 1.1, 0.9, 14.0}};
 constexpr int64_t kCUs = 256;
 constexpr int64_t kMaxLd = int64_t(1) << 22;   // 255 rows of it in 32 bits of bytes
+// Parts of at most 4,096 values of K round less than longer ones (a weight
+// gradient over 2.45M nodes: see the runs' bound in make_ssched) but number
+// M N K / 4,096, twice the output and more for a product that has tiles enough:
+// 80 GB for 2.45M x 4,096 over K = 8,192.  Beyond this much workspace K is cut
+// only as far as the machine has to be filled (at most three parts per slot).
+constexpr int64_t kMaxPartBytes = int64_t(256) << 20;
 
 // Time of `units` workgroups of `steps` steps: whole rounds of full CUs,
 // then a round with fewer workgroups on each CU.
@@ -1182,11 +1212,11 @@ SSched make_ssched(int64_t M, int64_t N, int64_t K, int64_t groups, int64_t mspl
   s.whole = s.tiles;
   s.full = 1;
   s.ipw = s.nk;
-  // K cut into parts: `ipw` steps each, at most c.max_run
-  auto cut = [&](int64_t tiles, int ipw) {
+  // K cut into parts of `ipw` steps (`most`: and no longer ones)
+  auto cut = [&](int64_t tiles, int ipw, int most) {
     int full = s.nk / ipw, rem = s.nk - full * ipw;
-    if (rem > 0 && (rem < c.min_steps / 2 || ipw == c.max_run)) {   // no sliver per tile; equal parts of a long K
-      const int q = rem < c.min_steps / 2 && (s.nk + full - 1) / full <= c.max_run ? full : full + 1;
+    if (rem > 0 && (rem < c.min_steps / 2 || ipw == most)) {   // no sliver per tile; equal parts of a long K
+      const int q = rem < c.min_steps / 2 && (s.nk + full - 1) / full <= most ? full : full + 1;
       ipw = (s.nk + q - 1) / q;
       full = s.nk / ipw;
       rem = s.nk - full * ipw;
@@ -1208,20 +1238,24 @@ SSched make_ssched(int64_t M, int64_t N, int64_t K, int64_t groups, int64_t mspl
   auto units = [&]() {
     return s.ragged * s.full + (s.rem > 0 ? (s.ragged * s.rem + s.ipw - 1) / s.ipw : 0);
   };
-  double us;
+  const SSched uncut = s;
+  double us = 0.0;
+  bool done = false;
   if (s.nk > c.max_run) {
     const int even = static_cast<int>(std::max<int64_t>((s.tiles * s.nk + slots - 1) / slots, c.min_steps));
-    cut(s.tiles, std::min(even, c.max_run));
+    cut(s.tiles, std::min(even, c.max_run), c.max_run);
     us = run_us(c, units(), s.ipw) + fix_us();
-  } else {
+    done = s.ragged * s.parts <= kMaxPartBytes / (int64_t(4) * c.bm * c.bn);
+    if (!done) s = uncut;
+  }
+  if (!done) {
     us = run_us(c, s.tiles, s.nk);
     const int ipw = static_cast<int>(std::max<int64_t>((r * s.nk + slots - 1) / slots, c.min_steps));
     if (r > 0 && ipw < s.nk) {   // the last, partly filled round cut in K, if that is quicker
-      const SSched keep = s;
-      cut(r, ipw);
+      cut(r, ipw, INT32_MAX);
       const double t = run_us(c, waves * slots, s.nk) + run_us(c, units(), s.ipw) + fix_us();
       if (t < us && s.ipw < s.nk) us = t;
-      else s = keep;
+      else s = uncut;
     }
   }
   if (cost) *cost = us;

@@ -149,7 +149,8 @@ struct GemmOut {
 // `groups` independent products of the same shape: group g reads A and B
 // and writes C at the pointers offset by g times their group strides.  A may
 // be a concatenation (p1) with ld1 == ld0, B may not; a row-contiguous A goes
-// with a row-contiguous B.  The workspace depends on where A is concatenated:
+// with a row-contiguous B.  The workspace (at most 256 MB or three partial
+// tiles per workgroup the GPU holds) depends on where A is concatenated:
 // msplit rows (a row-contiguous A) or ksplit values of K in its first part
 // (0: not concatenated).
 size_t gemm_workspace(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups = 1, int64_t msplit = 0,

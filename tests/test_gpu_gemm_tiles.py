@@ -109,3 +109,69 @@ def test_operands_up_to_the_largest(env, n, si, so, tile):
             rel = _rel(got, x, y)
             print(f"{a:.0e} {b:.0e} {what}: rel {rel:.2e}", flush=True)
             assert rel < 2e-6, (what, rel)
+
+
+def _chunked_rel(torch, got, a, b, rows=4096):
+    """Relative error of got = a b, and the mean of the error over its standard deviation; fp64 in
+    row chunks of a."""
+    num = den = total = 0.0
+    b = b.double()
+    for i in range(0, a.shape[0], rows):
+        e = a[i:i + rows].double() @ b
+        d = got[i:i + rows].double() - e
+        num += float(d.square().sum())
+        den += float(e.square().sum())
+        total += float(d.sum())
+    return (num / den) ** 0.5, total / got.numel() / (num / got.numel()) ** 0.5
+
+
+def _forward(env, H, W):
+    torch, G, ctx = env
+    n, si = H.shape
+    A, keep = _identity(env, n)
+    d = G.layer_desc(G.GIST_LAYER_GCN, G.GIST_ACT_NONE, n, si, W.shape[1], order=G.GIST_ORDER_AGG_FIRST)
+    ws = torch.empty(max(G.gist_layer_workspace_size(d)[0], 1), dtype=torch.uint8, device="cuda")
+    agg, out = torch.empty_like(H), torch.empty(n, W.shape[1], device="cuda")
+    G.gist_profile_begin(ctx)
+    G.gist_gcn_layer_fwd(ctx, d, A, H, W, agg, out, ws)
+    names = set(G.gist_profile_read(ctx)[0])
+    G.gist_profile_end(ctx)
+    del keep
+    return out, names
+
+
+@pytest.mark.parametrize("n,si,so,tile,bound", [(8192, 8192, 8192, 256, 7e-7), (65600, 65536, 64, 64, 2e-6)])
+def test_long_whole_tiles(env, n, si, so, tile, bound):
+    """A K beyond 4,096 whose parts would not fit the workspace: a workgroup keeps its tile and
+    turns the sign of its accumulators every 4,096 values, so that the unit's rounding toward minus
+    infinity cancels (without the turns the 256 x 256 tile's errors have a mean of about 0.16 of
+    their spread).  Bounds: 0.42 2^-24 sqrt(512 / 2) = 4.0e-7 for the large tile (one rounding
+    per step of 16), 0.42 2^-24 sqrt(2 4,096 / 2) = 1.6e-6 for the small one (two)."""
+    torch = env[0]
+    r = _randn(torch, 4)
+    H, W = r(n, si), r(si, so) * 0.02
+    out, names = _forward(env, H, W)
+    assert any(f"_{tile}x{tile}_" in k for k in names), names
+    rel, bias = _chunked_rel(torch, out, H, W)
+    print(f"rel {rel:.2e} mean / spread {bias:.3f} {sorted(names)}", flush=True)
+    assert rel < bound
+    assert abs(bias) < 0.05
+
+
+def test_long_weight_gradient_beyond_the_workspace(env):
+    """dW over 1.2M nodes: parts of 4,096 values of K would take 307 MB, so they are longer."""
+    torch = env[0]
+    n, w = 1200007, 512
+    r = _randn(torch, 5)
+    H, W, dZ = r(n, w), r(w, w) * 0.05, r(n, w)
+    _, dW, _, names = _gcn(env, H, W, dZ)
+    assert "gemm_fixup" in names, names
+    exact = torch.zeros(w, w, dtype=torch.float64, device="cuda")
+    for i in range(0, n, 1 << 17):
+        exact += H[i:i + (1 << 17)].double().t() @ dZ[i:i + (1 << 17)].double()
+    err = dW.double() - exact
+    rel = float(err.norm() / exact.norm())
+    print(f"rel {rel:.2e}", flush=True)
+    # 64 parts of 1,172 steps: 0.42 2^-24 sqrt(2 1,172 / 2) = 8.6e-7 at two roundings per step
+    assert rel < 2e-6
+    assert abs(float(err.mean())) < 6.0 / w * float(err.std())
