@@ -308,12 +308,12 @@ BwdPlan plan_bwd(const gist_layer_desc* L) {
   if (L->kind == GIST_LAYER_SAGE_MEAN || order == GIST_ORDER_AGG_FIRST) {
     p.tmp = fbytes(n, G * si);  // dP = dZ W^T (W_neigh for SAGE)
     // dW = X^T dZ, X = [H | Abar H] for SAGE: rows in two parts
-    p.gemm = std::max(gist::gemm_workspace(y.wrows, so, n, L->dtype, G, y.wrows > si ? si : 0),
-                      gist::gemm_workspace(n, y.wrows, so, L->dtype, G));
+    p.gemm = std::max(gist::gemm_workspace(y.wrows, so, n, y.ld_in, y.ld_out, L->dtype, G, y.wrows > si ? si : 0),
+                      gist::gemm_workspace(n, y.wrows, so, y.ld_out, so, L->dtype, G));
   } else {
     p.tmp = fbytes(n_in, G * so);  // Abar^T dZ
-    p.gemm = std::max(gist::gemm_workspace(si, so, n_in, L->dtype, G),
-                      gist::gemm_workspace(n_in, si, so, L->dtype, G));
+    p.gemm = std::max(gist::gemm_workspace(si, so, n_in, y.ld_in, y.ld_out, L->dtype, G),
+                      gist::gemm_workspace(n_in, si, so, y.ld_out, so, L->dtype, G));
   }
   return p;
 }
@@ -323,8 +323,8 @@ size_t plan_fwd(const gist_layer_desc* L) {
   const int order = resolve_order(L);
   if (L->kind == GIST_LAYER_GCN && order == GIST_ORDER_XFORM_FIRST)
     return align256(fbytes(y.n_in, y.G * y.so)) +
-           gist::gemm_workspace(y.n_in, y.so, y.si, L->dtype, y.G);
-  return gist::gemm_workspace(y.n, y.so, y.wrows, L->dtype, y.G, 0, y.wrows > y.si ? y.si : 0);
+           gist::gemm_workspace(y.n_in, y.so, y.si, y.ld_in, y.so, L->dtype, y.G);
+  return gist::gemm_workspace(y.n, y.so, y.wrows, y.ld_in, y.so, L->dtype, y.G, 0, y.wrows > y.si ? y.si : 0);
 }
 
 }  // namespace
@@ -591,13 +591,13 @@ GatPlan plan_gat_bwd(const gist_gat_desc* D) {
   p.alpha_t = fbytes(1, D->nnz);
   p.dp = fbytes(n, so);
   p.gemv = gist::gat_gemv_workspace(n, static_cast<int>(so));
-  p.gemm = std::max(gist::gemm_workspace(si, so, n, D->dtype),
-                    gist::gemm_workspace(n, si, so, D->dtype));
+  p.gemm = std::max(gist::gemm_workspace(si, so, n, si, so, D->dtype),
+                    gist::gemm_workspace(n, si, so, so, so, D->dtype));
   return p;
 }
 
 size_t plan_gat_fwd(const gist_gat_desc* D) {
-  return align256(fbytes(2, D->n)) + gist::gemm_workspace(D->n, D->s_out, D->s_in, D->dtype);
+  return align256(fbytes(2, D->n)) + gist::gemm_workspace(D->n, D->s_out, D->s_in, D->s_in, D->s_out, D->dtype);
 }
 
 }  // namespace

@@ -1262,7 +1262,13 @@ SSched make_ssched(int64_t M, int64_t N, int64_t K, int64_t groups, int64_t mspl
   return s;
 }
 
-int choose_cfg(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups, int64_t msplit, int64_t ksplit) {
+// Leading dimensions whose offsets inside a tile need more than 32 bits: only the
+// small kernel, which has 64-bit ones, takes them.
+bool far_ld(int64_t lda, int64_t ldb) { return lda >= kMaxLd || ldb >= kMaxLd; }
+
+int choose_cfg(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups, int64_t msplit, int64_t ksplit,
+               bool far) {
+  if (far) return dtype == GIST_DTYPE_BF16_IN ? 4 : 2;
   const int lo = dtype == GIST_DTYPE_BF16_IN ? 3 : 0, hi = dtype == GIST_DTYPE_BF16_IN ? 6 : 3;
   int best = lo;
   double bc = 1e300;
@@ -1294,12 +1300,12 @@ int vec_of(const Operand& o, int64_t R, int64_t K) {
 
 }  // namespace
 
-size_t gemm_workspace(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups, int64_t msplit,
-                      int64_t ksplit) {
+size_t gemm_workspace(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int dtype, int64_t groups,
+                      int64_t msplit, int64_t ksplit) {
   if (M <= 0 || N <= 0 || K <= 0 || groups <= 0) return 0;
   if (msplit <= 0) msplit = M;
   if (ksplit <= 0) ksplit = K;
-  const Cfg& c = kCfg[choose_cfg(M, N, K, dtype, groups, msplit, ksplit)];
+  const Cfg& c = kCfg[choose_cfg(M, N, K, dtype, groups, msplit, ksplit, far_ld(lda, ldb))];
   const SSched s = make_ssched(M, N, K, groups, msplit, ksplit, c, nullptr);
   return static_cast<size_t>(s.ragged) * s.parts * c.bm * c.bn * sizeof(float);
 }
@@ -1315,17 +1321,9 @@ gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K, const Operand&
     return set_error(GIST_E_UNSUPPORTED, "gemm: operand form");
   const int64_t msplit = !A.k_major && A.p1 ? std::min(A.split, M) : M;
   const int64_t ksplit = A.k_major && A.p1 ? std::min(A.split, K) : K;
-  int ci = choose_cfg(M, N, K, dtype, groups, msplit, ksplit);
-  // 32-bit offsets inside a tile; past them the small kernel, which has 64-bit
-  // ones, with whole tiles
-  const bool far = (ci < 2 || ci == 5) && (A.ld0 >= kMaxLd || B.ld0 >= kMaxLd);
-  if (far) ci = bf ? 4 : 2;
+  const int ci = choose_cfg(M, N, K, dtype, groups, msplit, ksplit, far_ld(A.ld0, B.ld0));
   const Cfg& c = kCfg[ci];
-  SSched s = make_ssched(M, N, K, groups, msplit, ksplit, c, nullptr);
-  if (far) {
-    s.whole = s.tiles;
-    s.ragged = s.parts = s.rem = 0;
-  }
+  const SSched s = make_ssched(M, N, K, groups, msplit, ksplit, c, nullptr);
   const size_t need = static_cast<size_t>(s.ragged) * s.parts * c.bm * c.bn * sizeof(float);
   if (need > 0 && (!ws || ws_bytes < need))
     return set_error(GIST_E_NOMEM, "gemm: workspace too small");

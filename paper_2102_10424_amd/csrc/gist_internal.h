@@ -150,11 +150,11 @@ struct GemmOut {
 // and writes C at the pointers offset by g times their group strides.  A may
 // be a concatenation (p1) with ld1 == ld0, B may not; a row-contiguous A goes
 // with a row-contiguous B.  The workspace (at most 256 MB or three partial
-// tiles per workgroup the GPU holds) depends on where A is concatenated:
-// msplit rows (a row-contiguous A) or ksplit values of K in its first part
-// (0: not concatenated).
-size_t gemm_workspace(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups = 1, int64_t msplit = 0,
-                      int64_t ksplit = 0);
+// tiles per workgroup the GPU holds) depends on the operands' leading
+// dimensions and on where A is concatenated: msplit rows (a row-contiguous A)
+// or ksplit values of K in its first part (0: not concatenated).
+size_t gemm_workspace(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int dtype, int64_t groups = 1,
+                      int64_t msplit = 0, int64_t ksplit = 0);
 gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K,
                  const Operand& A, const Operand& B, const GemmOut& C, int dtype,
                  void* ws, size_t ws_bytes, int64_t groups = 1);

@@ -175,3 +175,22 @@ def test_long_weight_gradient_beyond_the_workspace(env):
     # 64 parts of 1,172 steps: 0.42 2^-24 sqrt(2 1,172 / 2) = 8.6e-7 at two roundings per step
     assert rel < 2e-6
     assert abs(float(err.mean())) < 6.0 / w * float(err.std())
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_far_strides_with_a_long_reduction(env, dtype):
+    """Leading dimensions beyond 2^22 floats go to the small tile, which is cut in K like any
+    other: the forward's K of 2^22 + 16 (operands rounded first for bf16 inputs).  Whole tiles, which
+    such strides once forced, rounded 2^19 times over it."""
+    torch, G, ctx = env
+    n, si, so = 200, (1 << 22) + 16, 130
+    r = _randn(torch, 6)
+    H, W, dZ = r(n, si), r(si, so), r(n, so)
+    out, dW, dH, names = _gcn(env, H, W, dZ, dtype)
+    assert "gemm_fixup" in names and any("_64x64_" in k for k in names), names
+    if dtype:
+        H, W, dZ = (x.bfloat16().float() for x in (H, W, dZ))
+    for what, got, a, b in (("forward", out, H, W), ("dW", dW, H.t(), dZ), ("dH", dH, dZ, W.t())):
+        rel = _rel(got, a, b)
+        print(f"{what}: rel {rel:.2e}", flush=True)
+        assert rel < 2e-6, (what, rel)
