@@ -1178,6 +1178,7 @@ constexpr Cfg kCfg[] = {{256, 256, KS, 1, 8, kRunK / KS, 2.95, 1.75, 14.0},
                         {64, 64, 64, 3, 2, 1 << 20, 1.8, 0.8, 4.0},
                         {256, 256, 32, 1, 8, 1 << 20, 1.1, 0.9, 14.0}};
 constexpr int64_t kCUs = 256;
+constexpr unsigned threads_of(const Cfg& c) { return c.bm == 256 ? 512 : 256; }
 constexpr int64_t kMaxLd = int64_t(1) << 22;   // 255 rows of it in 32 bits of bytes
 // Parts of at most 4,096 values of K round less than longer ones (a weight
 // gradient over 2.45M nodes: see the runs' bound in make_ssched) but number
@@ -1262,6 +1263,10 @@ SSched make_ssched(int64_t M, int64_t N, int64_t K, int64_t groups, int64_t mspl
   return s;
 }
 
+int64_t sgrid(const SSched& s) {
+  return s.whole + s.ragged * s.full + (s.rem > 0 ? (s.ragged * s.rem + s.ipw - 1) / s.ipw : 0);
+}
+
 // Leading dimensions whose offsets inside a tile need more than 32 bits: only the
 // small kernel, which has 64-bit ones, takes them.
 bool far_ld(int64_t lda, int64_t ldb) { return lda >= kMaxLd || ldb >= kMaxLd; }
@@ -1274,14 +1279,11 @@ int choose_cfg(int64_t M, int64_t N, int64_t K, int dtype, int64_t groups, int64
   double bc = 1e300;
   for (int i = lo; i < hi; ++i) {
     double c;
-    make_ssched(M, N, K, groups, msplit, ksplit, kCfg[i], &c);
+    const SSched s = make_ssched(M, N, K, groups, msplit, ksplit, kCfg[i], &c);
+    if (sgrid(s) > UINT32_MAX / threads_of(kCfg[i])) c += 1e200;   // a grid holds fewer than 2^32 threads
     if (c < bc) { bc = c; best = i; }
   }
   return best;
-}
-
-int64_t sgrid(const SSched& s) {
-  return s.whole + s.ragged * s.full + (s.rem > 0 ? (s.ragged * s.rem + s.ipw - 1) / s.ipw : 0);
 }
 
 // Floats per load along the operand's contiguous dimension (4, 2 or 1).
@@ -1376,7 +1378,7 @@ gist_status gemm(hipStream_t st, int64_t M, int64_t N, int64_t K, const Operand&
     else if (va == 2) GIST_LARGE(AK_, BK_, 2);            \
     else GIST_LARGE(AK_, BK_, 1);                         \
   } while (0)
-    const unsigned thr = c.bm == 256 ? 512 : 256;
+    const unsigned thr = threads_of(c);
     if (A.k_major && B.k_major) GIST_SPLIT_V(true, true);
     else if (A.k_major) GIST_SPLIT_V(true, false);
     else GIST_SPLIT_V(false, false);

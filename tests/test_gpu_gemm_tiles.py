@@ -194,3 +194,33 @@ def test_far_strides_with_a_long_reduction(env, dtype):
         rel = _rel(got, a, b)
         print(f"{what}: rel {rel:.2e}", flush=True)
         assert rel < 2e-6, (what, rel)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_rows_beyond_one_grid_of_small_tiles(env, dtype):
+    """A layer-sampled forward over 2^30 + 70 input rows: 2^24 tiles of 64 rows would be 2^32
+    threads, more than one grid holds, so a larger tile takes the product."""
+    torch, G, ctx = env
+    n, n_in, si, so = 64, (1 << 30) + 70, 2, 1
+    print(f"n_in={n_in} dtype={dtype}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    H = torch.randn(n_in, si, generator=g, device="cuda")
+    W = torch.randn(si, so, generator=g, device="cuda")
+    col = torch.randint(0, n_in, (n, 4), generator=g, device="cuda")
+    col[:, 3] = n_in - 1 - torch.arange(n, device="cuda")     # the last rows of all
+    col = col.sort(1).values
+    val = torch.randn(n, 4, generator=g, device="cuda")
+    rp, c32 = torch.arange(0, 4 * n + 1, 4, dtype=torch.int32, device="cuda"), col.int().reshape(-1)
+    A = G.csr_dev(n, 4 * n, rp, c32, val)
+    d = G.layer_desc(G.GIST_LAYER_GCN, G.GIST_ACT_NONE, n, si, so, dtype, order=G.GIST_ORDER_XFORM_FIRST,
+                     n_in=n_in)
+    ws = torch.empty(max(G.gist_layer_workspace_size(d)[0], 1), dtype=torch.uint8, device="cuda")
+    out = torch.empty(n, so, device="cuda")
+    G.gist_gcn_layer_fwd(ctx, d, A, H, W, None, out, ws)
+    torch.cuda.synchronize()
+    h, w = H[col.reshape(-1)], W
+    if dtype:
+        h, w = h.bfloat16(), w.bfloat16()
+    exact = ((h.double() @ w.double()).reshape(n, 4) * val.double()).sum(1, keepdim=True)
+    # at most 2 + 4 fp32 roundings of terms of the result's size
+    assert float((out.double() - exact).norm() / exact.norm()) < 2e-6
