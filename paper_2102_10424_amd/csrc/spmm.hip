@@ -10,9 +10,11 @@
 // into column tiles.  Blocks are ordered XCD-major, column tile major: each
 // XCD's L2 sees a contiguous range of rows of one column slab at a time
 // (block-ordered graphs keep neighbours close).
-// No atomics: every output element is written by exactly one lane, and the
-// nonzeros of a row are summed in storage order, so results are bitwise
-// reproducible.
+// No atomics: every output element is written by exactly one lane.  A row of
+// up to kLongRow nonzeros is summed in storage order, a longer one in kSegs
+// parts, each in storage order, added in order.  The order is a function of
+// the row's length alone: not of the widths, alignments or entry counts that
+// choose a kernel, so results are bitwise reproducible across all of them.
 
 #include <cstdio>
 #include <type_traits>
@@ -65,6 +67,15 @@ __device__ __forceinline__ void store_vec(float* p, const float (&x)[VEC]) {
 // of 1,234 entries alone kept one wave for 109 us on a 20,000-node power-law
 // graph whose other rows took a few (512 columns; now 42 us for the call).
 constexpr int kLongRow = 128;
+constexpr int kSegs = 16;   // one for each lane group of a wave of the narrowest rows
+
+// Part q of a long row's entries r0 .. r1: whole batches of eight.
+__device__ __forceinline__ void segment(int r0, int r1, int q, int& b, int& e) {
+  const unsigned len = static_cast<unsigned>(r1 - r0);
+  const unsigned seg = (len + 8 * kSegs - 1) / (8 * kSegs) * 8;
+  b = r0 + static_cast<int>(min(q * seg, len));
+  e = r0 + static_cast<int>(min((q + 1) * seg, len));
+}
 
 // Row of slot s (of `slots` in a block): consecutive rows share a block, so
 // that their common neighbours' rows meet in one CU's L1; on sparse graphs
@@ -117,10 +128,10 @@ __global__ __launch_bounds__(256) void spmm_kernel(
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
 
-  // The entries base .. base + cnt (1 <= cnt <= LPR, the same for the whole
-  // group): lane gl of the group loads one, then the group reads them back by
-  // shuffle, four gathers in flight.
-  auto window = [&](int base, int cnt) {
+  // Adds the entries base .. base + cnt (1 <= cnt <= LPR, the same for the whole
+  // group) to acc: lane gl of the group loads one, then the group reads them
+  // back by shuffle, four gathers in flight.
+  auto window = [&](float (&acc)[VEC], int base, int cnt) {
     int my_c = 0;
     float my_v = 0.f;
     if (gl < cnt) {
@@ -166,31 +177,34 @@ __global__ __launch_bounds__(256) void spmm_kernel(
       }
     }
   };
-  const bool is_long = RPW > 1 && spread && e1 - e0 > kLongRow;
+  const bool is_long = RPW > 1 && e1 - e0 > kLongRow;
   {
     const int end = is_long ? e0 : e1;
-    for (int base = e0; base < end; base += LPR) window(base, min(LPR, end - base));
+    for (int base = e0; base < end; base += LPR) window(acc, base, min(LPR, end - base));
   }
-  if (RPW > 1 && spread) {
-    // long rows: the wave's groups take their windows in turn, their sums
-    // are added across the groups
+  if constexpr (RPW > 1) {
+    static_assert(kSegs % RPW == 0, "");
+    // long rows: the wave's groups take the parts in turn
     unsigned long long todo = __ballot(is_long && gl == 0);
     while (todo) {
       const int owner = __ffsll(todo) - 1;
       todo &= todo - 1;
       const int l0 = __shfl(e0, owner, 64), l1 = __shfl(e1, owner, 64);
-      float keep[VEC];
+#pragma unroll 1
+      for (int p = 0; p < kSegs; p += RPW) {
+        float part[VEC];
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-        keep[v] = acc[v];
-        acc[v] = 0.f;
-      }
-      for (int base = l0 + grp * LPR; base < l1; base += 64) window(base, min(LPR, l1 - base));
+        for (int v = 0; v < VEC; ++v) part[v] = 0.f;
+        int b, e;
+        segment(l0, l1, p + grp, b, e);
+        for (int base = b; base < e; base += LPR) window(part, base, min(LPR, e - base));
+#pragma unroll 2
+        for (int q = 0; q < RPW; ++q)
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-#pragma unroll
-        for (int o = LPR; o < 64; o <<= 1) acc[v] += __shfl_xor(acc[v], o, 64);
-        if (owner / LPR != grp) acc[v] = keep[v];
+          for (int v = 0; v < VEC; ++v) {
+            const float x = __shfl(part[v], q * LPR + gl, 64);
+            acc[v] = owner / LPR == grp ? acc[v] + x : acc[v];
+          }
       }
     }
   }
@@ -213,15 +227,15 @@ __global__ __launch_bounds__(256) void spmm_kernel(
 // Wide rows (64 lanes per row): the row index is wave-uniform, so each
 // nonzero's (col, val) is broadcast with readlane into scalar registers and
 // the gather address is a scalar base plus the lane's column offset; eight
-// gathers are kept in flight per wave.  A long row's entries are shared by
-// the block's W waves and their sums added in wave order.
-template <int VEC, int W, bool LONG>
+// gathers are kept in flight per wave.  A long row's parts are shared by the
+// block's W waves.
+template <int VEC, int W, bool SPREAD>
 __global__ __launch_bounds__(64 * W) void spmm_wide_kernel(
     int n, const int* __restrict__ rowptr, const int* __restrict__ col,
     const float* __restrict__ val, const float* __restrict__ X, int64_t ldx, int width,
     float* Y, int64_t ldy, const float* add, int64_t ld_add, int relu, int col_tiles,
     int64_t nblocks, const float* mask, int64_t ldm) {
-  __shared__ float part[LONG ? W : 1][64 * VEC];
+  __shared__ float part[kSegs][64 * VEC];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t logical = xcd_remap(blockIdx.x, nblocks);
@@ -230,28 +244,25 @@ __global__ __launch_bounds__(64 * W) void spmm_wide_kernel(
   const int64_t rblocks = nblocks / col_tiles;
   const int ctile = static_cast<int>(logical / rblocks);
   const int64_t rblock = logical - static_cast<int64_t>(ctile) * rblocks;
-  const int64_t row = row_of(rblock, rblocks, wave, W, LONG);
+  const int64_t row = row_of(rblock, rblocks, wave, W, SPREAD);
   const bool inrow = row < n;
   const int c0 = ctile * (64 * VEC) + lane * VEC;
   const bool active = c0 < width;
-  int e0 = 0, e1 = 0;
-  unsigned longs = 0;
-  int s0 = 0, s1 = 0;   // LONG: lane w holds the extent of the block's row w, in every wave,
-                        // so the whole block knows the long ones without a barrier
-  if constexpr (LONG) {
-    const int64_t r = row_of(rblock, rblocks, lane % W, W, LONG);
+  // lane w holds the extent of the block's row w, in every wave, so the whole
+  // block knows the long ones without a barrier
+  int s0 = 0, s1 = 0;
+  {
+    const int64_t r = row_of(rblock, rblocks, lane % W, W, SPREAD);
     if (r < n) {
       s0 = rowptr[r];
       s1 = rowptr[r + 1];
     }
-    longs = static_cast<unsigned>(__ballot(lane < W && s1 - s0 > kLongRow));
-    if (!(longs >> wave & 1)) {
-      e0 = __builtin_amdgcn_readlane(s0, wave);
-      e1 = __builtin_amdgcn_readlane(s1, wave);
-    }
-  } else if (inrow) {
-    e0 = rowptr[row];
-    e1 = rowptr[row + 1];
+  }
+  const unsigned longs = static_cast<unsigned>(__ballot(lane < W && s1 - s0 > kLongRow));
+  int e0 = 0, e1 = 0;
+  if (!(longs >> wave & 1)) {
+    e0 = __builtin_amdgcn_readlane(s0, wave);
+    e1 = __builtin_amdgcn_readlane(s1, wave);
   }
   // Add and mask values load before the gathers (row and column clamped into
   // the matrix: every load is in bounds; an inactive lane's values are never stored)
@@ -311,25 +322,27 @@ __global__ __launch_bounds__(64 * W) void spmm_wide_kernel(
     }
   };
   gather(e0, e1);
-  if (LONG && longs) {
+  if (longs) {
     float keep[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) keep[v] = acc[v];
     for (int w = 0; w < W; ++w) {
       if (!(longs >> w & 1)) continue;
       const int r0 = __builtin_amdgcn_readlane(s0, w), r1 = __builtin_amdgcn_readlane(s1, w);
-      const int seg = ((r1 - r0 + 8 * W - 1) / (8 * W)) * 8;   // whole batches per wave
-      const int b = min(r0 + wave * seg, r1);
-      gather(b, min(b + seg, r1));
+      for (int q = wave; q < kSegs; q += W) {
+        int b, e;
+        segment(r0, r1, q, b, e);
+        gather(b, e);
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) part[LONG ? wave : 0][lane * VEC + v] = acc[v];
+        for (int v = 0; v < VEC; ++v) part[q][lane * VEC + v] = acc[v];
+      }
       __syncthreads();
       if (wave == w) {
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
-          float sum = part[0][lane * VEC + v];
+          float sum = 0.f;
 #pragma unroll
-          for (int q = 1; q < W; ++q) sum += part[LONG ? q : 0][lane * VEC + v];
+          for (int q = 0; q < kSegs; ++q) sum += part[q][lane * VEC + v];
           keep[v] = sum;
         }
       }
