@@ -78,12 +78,23 @@ __device__ __forceinline__ void segment(int r0, int r1, int q, int& b, int& e) {
 }
 
 // Row of slot s (of `slots` in a block): consecutive rows share a block, so
-// that their common neighbours' rows meet in one CU's L1; on sparse graphs
-// (`spread`, at most 16 entries per row on average) there is little to
-// share, and the rows of a block lie rblocks apart, so that the hubs of a
-// degree-ordered graph fall into different blocks.
-__device__ __forceinline__ int64_t row_of(int64_t rblock, int64_t rblocks, int s, int slots, int spread) {
-  return spread ? s * rblocks + rblock : rblock * slots + s;
+// that their common neighbours' rows meet in one CU's L1; with `apart` the rows
+// of a block lie rblocks apart, so that the hubs of a degree-ordered graph
+// fall into different blocks.
+__device__ __forceinline__ int64_t row_of(int64_t rblock, int64_t rblocks, int s, int slots, bool apart) {
+  return apart ? s * rblocks + rblock : rblock * slots + s;
+}
+
+// Whether the first or the last 64th of the rows holds more than four times
+// its share of the entries: a graph ordered by degree (scalar loads of the
+// same three words in every block).  On a 20,000-node power-law graph ordered
+// by degree, rows apart take 17 us at 16 columns and 39 at 512, consecutive
+// ones 61 and 88; on 1M nodes in clusters of 150 (10 entries per row) rows
+// apart take 82 us at 8 columns and 1,800 at 512, consecutive ones 43 and 1,640.
+__device__ __forceinline__ bool skewed(const int* __restrict__ rowptr, int n) {
+  const int64_t total = rowptr[n], slice = n / 64;
+  return 16 * static_cast<int64_t>(rowptr[slice]) > total ||
+         16 * (total - rowptr[n - slice]) > total;
 }
 
 template <int VEC, int LPR>
@@ -104,7 +115,7 @@ __global__ __launch_bounds__(256) void spmm_kernel(
   const int64_t rblocks = nblocks / col_tiles;
   const int ctile = static_cast<int>(logical / rblocks);
   const int64_t rblock = logical - static_cast<int64_t>(ctile) * rblocks;
-  const int64_t row = row_of(rblock, rblocks, wave * RPW + grp, kWaves * RPW, spread);
+  const int64_t row = row_of(rblock, rblocks, wave * RPW + grp, kWaves * RPW, spread && skewed(rowptr, n));
   const int c0 = ctile * (LPR * VEC) + gl * VEC;
   const bool incol = c0 < width;
   const bool active = row < n && incol;
@@ -244,19 +255,25 @@ __global__ __launch_bounds__(64 * W) void spmm_wide_kernel(
   const int64_t rblocks = nblocks / col_tiles;
   const int ctile = static_cast<int>(logical / rblocks);
   const int64_t rblock = logical - static_cast<int64_t>(ctile) * rblocks;
-  const int64_t row = row_of(rblock, rblocks, wave, W, SPREAD);
-  const bool inrow = row < n;
   const int c0 = ctile * (64 * VEC) + lane * VEC;
   const bool active = c0 < width;
   // lane w holds the extent of the block's row w, in every wave, so the whole
-  // block knows the long ones without a barrier
+  // block knows the long ones without a barrier; with SPREAD lane W + w holds
+  // that of its row in the other placement, so that neither load waits
   int s0 = 0, s1 = 0;
   {
-    const int64_t r = row_of(rblock, rblocks, lane % W, W, SPREAD);
+    const int64_t r = row_of(rblock, rblocks, lane % W, W, SPREAD && (lane & W));
     if (r < n) {
       s0 = rowptr[r];
       s1 = rowptr[r + 1];
     }
+  }
+  const bool apart = SPREAD && skewed(rowptr, n);
+  const int64_t row = row_of(rblock, rblocks, wave, W, apart);
+  const bool inrow = row < n;
+  if (SPREAD && apart) {
+    s0 = __shfl(s0, lane | W, 64);
+    s1 = __shfl(s1, lane | W, 64);
   }
   const unsigned longs = static_cast<unsigned>(__ballot(lane < W && s1 - s0 > kLongRow));
   int e0 = 0, e1 = 0;
@@ -287,18 +304,15 @@ __global__ __launch_bounds__(64 * W) void spmm_wide_kernel(
         my_c = col[base + lane];
         my_v = val[base + lane];
       }
-      // U gathers in flight; REST: the loads past cnt repeat its last entry and
-      // are not added
-      auto batch = [&](auto unroll, auto rest, int j) {
+      // U gathers in flight
+      auto batch = [&](auto unroll, int j) {
         constexpr int U = decltype(unroll)::value;
-        constexpr bool REST = decltype(rest)::value;
         int cj[U];
         float vj[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int k = REST ? min(j + u, cnt - 1) : j + u;
-          cj[u] = __builtin_amdgcn_readlane(my_c, k);
-          vj[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), k));
+          cj[u] = __builtin_amdgcn_readlane(my_c, j + u);
+          vj[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_v), j + u));
         }
         if (active) {
           float x[U][VEC];
@@ -306,19 +320,19 @@ __global__ __launch_bounds__(64 * W) void spmm_wide_kernel(
           for (int u = 0; u < U; ++u) load_vec<VEC>(Xc + static_cast<int64_t>(cj[u]) * ldx, x[u]);
 #pragma unroll
           for (int u = 0; u < U; ++u)
-            if (!REST || j + u < cnt) {
 #pragma unroll
-              for (int v = 0; v < VEC; ++v) acc[v] = fmaf(vj[u], x[u][v], acc[v]);
-            }
+            for (int v = 0; v < VEC; ++v) acc[v] = fmaf(vj[u], x[u][v], acc[v]);
         }
       };
       int j = 0;
-      for (; j + 8 <= cnt; j += 8) batch(std::integral_constant<int, 8>{}, std::false_type{}, j);
+      for (; j + 8 <= cnt; j += 8) batch(std::integral_constant<int, 8>{}, j);
       if (j + 4 <= cnt) {
-        batch(std::integral_constant<int, 4>{}, std::false_type{}, j);
+        batch(std::integral_constant<int, 4>{}, j);
         j += 4;
       }
-      if (j < cnt) batch(std::integral_constant<int, 3>{}, std::true_type{}, j);
+      if (j + 3 == cnt) batch(std::integral_constant<int, 3>{}, j);
+      else if (j + 2 == cnt) batch(std::integral_constant<int, 2>{}, j);
+      else if (j + 1 == cnt) batch(std::integral_constant<int, 1>{}, j);
     }
   };
   gather(e0, e1);
@@ -373,8 +387,9 @@ gist_status launch(hipStream_t st, int64_t n, int64_t nnz, const int32_t* rowptr
                    const float* val, const float* X, int64_t ldx, int width, float* Y,
                    int64_t ldy, const float* add, int64_t ld_add, bool relu, const float* mask,
                    int64_t ldm) {
-  // sparse matrices: rows spread over the blocks, and (wide rows) eight waves
-  // per block to share a hub
+  // sparse matrices may have hubs: rows apart if they come first (see skewed), and
+  // (wide rows) eight waves per block to share one: with four, 512 columns
+  // of a 20,000-node power-law graph took 50 us instead of 40
   const int spread = nnz <= 16 * n ? 1 : 0;
   const int waves = LPR == 64 && spread ? 8 : 4;
   constexpr int RPW = 64 / LPR;
