@@ -35,7 +35,10 @@
 // Inf in bf16 when scaled (from 2^104 on), leaves NaN in the tile, and sums
 // from 2^80 on overflow; so a wave whose accumulators hold anything non-finite
 // recomputes its block with the fp32 matrix instruction straight from memory.
-// No other input takes that path.
+// No other input takes that path.  It is slow: of the products of a 4,096-wide GCN
+// layer with 1,630 nodes, one NaN in H takes the forward from 350 to 1,200 us and
+// dW from 300 to 700 (one such column or row is in every tile row or column),
+// W all NaN dH from 330 to 1,700 (fp32 instruction throughout: 515, 510 and 515).
 //
 // bf16-input products round the operands (nearest even) on the same way to LDS
 // and take one product: gemm_bf16_kernel (256 x 256 tiles) and

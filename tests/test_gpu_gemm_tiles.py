@@ -224,3 +224,41 @@ def test_rows_beyond_one_grid_of_small_tiles(env, dtype):
     exact = ((h.double() @ w.double()).reshape(n, 4) * val.double()).sum(1, keepdim=True)
     # at most 2 + 4 fp32 roundings of terms of the result's size
     assert float((out.double() - exact).norm() / exact.norm()) < 2e-6
+
+
+@pytest.mark.parametrize("n,si,so,tile", [(70, 40, 51, 64), (3100, 602, 1024, 128), (4095, 610, 4095, 256)])
+def test_nonfinite_values_on_every_tile(env, n, si, so, tile):
+    """Inf, NaN and values whose scaled parts overflow, in either operand of each product: as in
+    fp32 arithmetic they reach their own row or column only, and the rest is as accurate as ever."""
+    torch = env[0]
+    inf, nan = float("inf"), float("nan")
+    r = _randn(torch, 9)
+    H, W, dZ = r(n, si), r(si, so) * 0.02, r(n, so)
+    H[:, 7] = H[:, 7].abs() + 0.1
+    W[5] = W[5].abs() + 0.1
+    H[3, 5], H[n - 1, 5], H[20, 6], H[31, 2] = inf, -inf, nan, 3e38   # rows of the forward, columns 2, 5, 6 of dW^T
+    W[7, so - 1], W[7, 11] = inf, nan                                 # its columns
+    out, dW, dH, names = _gcn(env, H, W, dZ)
+    assert any(f"_{tile}x{tile}_" in k for k in names), names
+    bad_r = torch.tensor([3, 20, n - 1], device="cuda")
+    bad_c = torch.tensor([11, so - 1], device="cuda")
+    good_c = torch.ones(so, dtype=torch.bool, device="cuda")
+    good_c[bad_c] = False
+    good_r = torch.ones(n, dtype=torch.bool, device="cuda")
+    good_r[bad_r] = False
+    assert bool(torch.isposinf(out[3, good_c]).all()) and bool(torch.isneginf(out[n - 1, good_c]).all())
+    assert bool(torch.isnan(out[20]).all()) and bool(torch.isnan(out[:, 11]).all())
+    assert bool(torch.isposinf(out[good_r, so - 1]).all())
+    good_r[31] = False                                                # 3e38: finite sums, checked alone
+    e = H[31].double() @ W[:, good_c].double()
+    assert float((out[31, good_c].double() - e).norm() / e.norm()) < 2e-6
+    assert _rel(out[good_r][:, good_c], H[good_r], W[:, good_c]) < 2e-6
+    cols = torch.ones(si, dtype=torch.bool, device="cuda")
+    cols[[5, 6]] = False
+    assert not bool(torch.isfinite(dW[[5, 6]]).any())
+    cols[2] = False
+    assert _rel(dW[cols], H[:, cols].t(), dZ) < 2e-6
+    keep = torch.ones(si, dtype=torch.bool, device="cuda")
+    keep[7] = False
+    assert not bool(torch.isfinite(dH[:, 7]).any())
+    assert _rel(dH[:, keep], dZ, W[keep].t()) < 2e-6
