@@ -44,7 +44,7 @@ CASES = [
     ("sage", "sbm1500", 4, 64, 32, 1, 0, False, False, "f32"),
     ("sage", "sbm1500", 3, 20, 48, 1, 0, True, False, "f32"),   # SAGE input layer
     ("sage", "sbm1500", 2, 32, 5, 0, 0, False, True, "f32"),
-    ("sage", "sbm1500", 2, 520, 520, 1, 0, False, False, "bf16"),   # packed bf16, per group
+    ("sage", "sbm1500", 2, 520, 520, 1, 0, False, False, "bf16"),   # bf16, groups in one grid
 ]
 
 

@@ -2,11 +2,10 @@
 into the weight-gradient GEMM's epilogue.  Its updated weights and input
 gradient must be bitwise those of gist_gcn_layer_bwd followed by
 gist_sgd_update (the epilogue applies the same fmaf to the same fp32 sum),
-for every GEMM path the weight gradient can take: direct tiles and stream-K
-partial tiles with their fix-up, node-contiguous copies of the operands
-(large fp32 dW), grouped sub-GCNs, rectangular layers, transform-first GCN,
-and the bf16-input kernels (packed and in-kernel rounding).  The plain path
-is held against the fp64 oracle elsewhere; one case here also checks the
+for the paths the weight gradient can take: whole tiles and tiles cut in K
+with their fix-up, grouped sub-GCNs, rectangular layers, transform-first GCN,
+and bf16 inputs (test_gpu_gemm_variants holds the updated weights of every
+kernel against fp64).  The plain path is held against the fp64 oracle elsewhere; one case here also checks the
 step itself against the oracle's SGD."""
 
 import numpy as np
@@ -109,14 +108,14 @@ def same(a, b):
 
 CASES = [
     # kind, graph, s_in, s_out, order, dtype, groups
-    ("gcn", "sbm1500", 100, 256, "agg", "f32", 1),     # dW 100 x 256 over K = 1500: stream-K
+    ("gcn", "sbm1500", 100, 256, "agg", "f32", 1),     # dW 100 x 256 cut over K = 1500
     ("gcn", "cl2000", 300, 64, "xform", "f32", 1),     # transform-first
     ("sage", "sbm1500", 128, 96, "agg", "f32", 1),
-    ("sage", "sbm1100", 1024, 1024, "agg", "f32", 1),  # node-contiguous dW operands
+    ("sage", "sbm1100", 1024, 1024, "agg", "f32", 1),  # dW 2048 x 1024 in whole tiles
     ("gcn", "sbm1500", 64, 48, "agg", "f32", 3),       # grouped sub-GCNs
-    ("sage", "sbm1500", 512, 512, "agg", "bf16", 1),   # packed bf16 kernel
-    ("sage", "sbm1500", 1024, 1024, "agg", "bf16", 1),  # 2048 x 1024 dW, rows of 1500 nodes
-    ("gcn", "sbm1500", 100, 64, "agg", "bf16", 1),     # bf16 rounding in the fp32 tiles
+    ("sage", "sbm1500", 512, 512, "agg", "bf16", 1),   # 64 x 64 tiles cut in K
+    ("sage", "sbm1500", 1024, 1024, "agg", "bf16", 1),  # 2048 x 1024 dW, whole 128 x 128 tiles
+    ("gcn", "sbm1500", 100, 64, "agg", "bf16", 1),     # two tiles in 12 parts
 ]
 
 

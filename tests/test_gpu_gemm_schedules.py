@@ -1,20 +1,13 @@
-"""GPU parity of the fp32 GEMM work schedules at their boundaries.
+"""GPU parity of the fp32 products over many nodes.
 
-The layer entry points pick one of several schedules for each dense product
-of eq. (2) and its backward pass, by shape:
-- whole 128 x 128 tiles per workgroup (many tiles), or stream-K ranges of
-  (tile, K step) iterations with partial tiles summed by a fix-up;
-- K slices dealt out slice-major when a product has at most 64 tiles and
-  at least 16 K steps (weight gradients reduced over many nodes);
-- for N <= 64, the K step of each tile split between the two halves of the
-  workgroup's waves, added through LDS before the epilogue;
-- for weight gradients with M, N >= 1024, node-contiguous operand copies
-  zero-padded to whole K steps.
-Each case below sits on one side of one of these boundaries (N = 1, 64, 65;
-64 against 72 tiles; K ragged or whole) and compares the forward and
-backward outputs with the fp64 oracle within 1e-4, the ReLU decisions of
-the backward taken from the oracle's forward values (as in
-``test_gpu_layers``).
+The layer entry points give each dense product of eq. (2) and its backward
+pass a tile (256, 128 or 64 wide) and a schedule by shape: whole tiles where
+there are many, tiles cut in K where there are few and K is long (a weight
+gradient reduced over the nodes), the parts summed by a second kernel.
+The cases below have 4,000 to 20,011 nodes, one, 47, 64, 65 or 1,024 output
+columns, and whole and ragged K, and compare the forward and backward outputs
+with the fp64 oracle within 1e-4, the ReLU decisions of the backward taken
+from the oracle's forward values (as in ``test_gpu_layers``).
 """
 
 import pytest
@@ -52,14 +45,12 @@ def graph(n):
 
 CASES = [
     # graph nodes, s_in, s_out, order (0 auto, 1 aggregate first, 2 transform first), what it reaches
-    (20011, 512, 64, 1, "forward 157 x 1 tiles, stream-K partial tiles, N = 64 narrow; "
-                        "dW 4 tiles sliced over ragged K = 20011, narrow"),
-    (20011, 300, 1, 1, "N = 1: narrow forward and dW, dW sliced (3 tiles)"),
-    (20011, 300, 65, 1, "N = 65: one 128-wide tile, not narrow; dW sliced"),
-    (4000, 200, 47, 2, "transform first: XW narrow (47), Abar^T dZ then dW sliced over 4000"),
-    (20000, 1024, 1024, 1, "dW 8 x 8 = 64 tiles: sliced, node-contiguous copies, K whole"),
-    (20011, 1040, 1024, 1, "dW 9 x 8 = 72 tiles: stream-K, node-contiguous copies padded "
-                           "from 20011 to 20032 nodes"),
+    (20011, 512, 64, 1, "forward 313 whole 64 x 64 tiles; dW 8 tiles in 79 parts over ragged K = 20011"),
+    (20011, 300, 1, 1, "N = 1: one column of a 64 x 64 tile; dW 5 tiles in 105 parts"),
+    (20011, 300, 65, 1, "N = 65: a second tile with one column; dW 10 tiles in 63 parts"),
+    (4000, 200, 47, 2, "transform first: XW (47 columns), Abar^T dZ then dW cut over 4000"),
+    (20000, 1024, 1024, 1, "128 x 128 tiles: forward and dH whole, dW 64 tiles cut in K"),
+    (20011, 1040, 1024, 1, "the same with ragged tile rows and K: dW 72 tiles over 20011"),
 ]
 
 

@@ -1,6 +1,6 @@
 """The fp32 products on the bf16 matrix cores (three bf16 parts per value, six
 products), through the layer calls of the C ABI with the identity as the
-graph's matrix, so that the forward is relu(H W), dW = H^T dZ, dH = dZ W^T.
+graph's matrix, so that the forward is H W, dW = H^T dZ, dH = dZ W^T.
 
 Bounds.  A product's dropped terms are below 3 * 2^-25 |a b|, and each of the
 at most 12 additions per 16 values of K, and of the additions of K parts,
@@ -24,15 +24,14 @@ def env():
     return torch, G, G.Context(0)
 
 
-def _layer(env, H, W, dZ, relu=False, sgd=None):
+def _layer(env, H, W, dZ):
     torch, G, ctx = env
     n, si = H.shape
     so = W.shape[1]
     rp = torch.arange(n + 1, dtype=torch.int32, device="cuda")
     one = torch.ones(n, device="cuda")
     A = G.csr_dev(n, n, rp, rp, one)
-    d = G.layer_desc(G.GIST_LAYER_GCN, G.GIST_ACT_RELU if relu else G.GIST_ACT_NONE, n, si, so,
-                     order=G.GIST_ORDER_AGG_FIRST)
+    d = G.layer_desc(G.GIST_LAYER_GCN, G.GIST_ACT_NONE, n, si, so, order=G.GIST_ORDER_AGG_FIRST)
     ws = torch.empty(max(*G.gist_layer_workspace_size(d), 1), dtype=torch.uint8, device="cuda")
     agg, out = torch.empty_like(H), torch.full((n, so), 7.0, device="cuda")
     dW, dH = torch.full_like(W, 7.0), torch.full_like(H, 7.0)
@@ -55,8 +54,9 @@ def _check(torch, got, A, B, what):
     assert rel < 2e-6, (what, rel)
 
 
-# edges of the 64 / 128 / 256 tiles and of the 16 / 64 K steps, odd and even
-# strides, a K beyond 4,096 (parts of alternating sign), a long reduction
+# edges of the 64 / 128 tiles and of the 16 / 64 K steps, odd and even strides, a
+# K beyond 4,096 (parts of alternating sign), a long reduction (the 256 tile and
+# every load width: test_gpu_gemm_variants)
 SHAPES = [(1, 1, 1), (63, 64, 65), (65, 63, 64), (129, 15, 130), (127, 130, 47), (255, 602, 66),
           (257, 256, 258), (1030, 8, 1030), (300, 4500, 40), (40, 17, 4500), (70001, 20, 33),
           (1630, 1024, 4096), (3100, 602, 1023)]

@@ -108,7 +108,7 @@ CASES = [
     ("sage", "sbm1500", 100, 256, 1, 0),
     ("sage", "sbm1500", 602, 260, 1, 0),
     ("sage", "cl2000", 256, 41, 0, 0),
-    # weight gradients large enough (M, N >= 1024) for node-contiguous operand copies
+    # weight gradients of at least 1024 x 1024
     ("sage", "sbm1500", 512, 1024, 1, 0),
     ("gcn", "er300", 1030, 1100, 1, 1),
     ("gcn", "sbm1500", 1100, 1030, 0, 2),
@@ -132,12 +132,12 @@ def test_layer_fp32(G, ctx, case):
         assert e <= FP32_TOL, (k, e)
 
 
-# bf16 cases include products large enough for the 256 x 256-tile MFMA path,
-# with ragged M / N / K, K split into several slices (one shorter than the
-# others) and the [dH | dP] split output of the SAGE backward; the last three
-# have weight gradients of at least 1024 x 1024 over ragged node counts (300,
-# 1500, 2000), read row-contiguous (the fp32 path copies such operands
-# node-contiguous first; for bf16 inputs that measured slower).
+# bf16 cases include ragged M / N / K, K cut into several parts (one shorter
+# than the others) and the [dH | dP] split output of the SAGE backward; the
+# last three have weight gradients of at least 1024 x 1024 over ragged node
+# counts (300, 1500, 2000).  Their tiles are 64 and 128 wide; the 256 wide ones
+# are in test_gpu_gemm_variants, which also rounds the operands first and
+# so can hold the products to fp32 level.
 @pytest.mark.parametrize("case", [("sage", "sbm1500", 100, 256, 1, 0),
                                   ("gcn", "cl2000", 500, 512, 1, 0),
                                   ("sage", "sbm1500", 602, 520, 1, 0),
@@ -158,15 +158,13 @@ def test_layer_bf16_inputs(G, ctx, case):
         assert e <= BF16_TOL, (k, e)
 
 
-def test_bf16_direct_and_packed_staging_bitwise(G, ctx):
-    """The bf16 product kernel stages operands straight from fp32 memory when
-    the 16-byte loads allow it, else from a rounded bf16 copy made by a
-    conversion pass; both put the same bf16 values in the same tiles.  A
-    transform-first GCN layer reads H as the forward product's K-contiguous
-    operand: H 16-byte aligned takes the direct staging, the same values at
-    a 4-byte offset take the conversion pass.  Forward and backward outputs
-    agree bit for bit (the backward's K = n products take the direct path in
-    both runs, with a ragged last K step: n = 2000 = 62 * 32 + 16)."""
+def test_bf16_load_widths_bitwise(G, ctx):
+    """The bf16 product kernels load 16, 8 or 4 bytes per lane as the alignment
+    allows and put the same bf16 values in the same tiles.  A transform-first
+    GCN layer reads H as the forward product's K-contiguous operand and as
+    dW's row-contiguous one: 16-byte aligned, and the same values at a 4-byte
+    offset.  Forward and backward outputs agree bit for bit (n = 2000 leaves a
+    ragged last K step)."""
     import torch
     g = GRAPHS["cl2000"]
     csr = MB.build(g, None, "gcn")
@@ -199,7 +197,7 @@ def test_bf16_direct_and_packed_staging_bitwise(G, ctx):
         assert a.tobytes() == b.tobytes()
     f = OL.gcn_forward(csr, H.astype(np.float64), W.astype(np.float64), True)
     e = relerr(outs[0][0], f["H_out"])
-    log(f"direct and packed staging bitwise; H_out vs oracle {e:.3e}")
+    log(f"16-byte and 4-byte loads bitwise; H_out vs oracle {e:.3e}")
     assert e <= BF16_TOL
 
 

@@ -5,8 +5,8 @@
   dH with every entry whose H <= 0 set to +0 (the select the separate
   ReLU-derivative pass makes) -- through each kernel that can write dH: the
   transposed aggregation (GCN aggregate-first, SAGE with its Add, gather and
-  matrix-core paths), the dH product of a transform-first GCN layer (fp32
-  stream-K tiles with fix-up, the bf16 kernels), grouped sub-GCNs and
+  matrix-core paths), the dH product of a transform-first GCN layer (fp32 and
+  bf16 inputs), grouped sub-GCNs and
   rectangular layers; also through the fused-SGD entry point.
 * DZ_IN: a hidden layer handed dZ = dH_out * 1[H_out > 0] with H_out = NULL
   gives bitwise the dW and dH of the plain call with dH_out and H_out.
@@ -42,13 +42,13 @@ CASES = [
     # kind, graph, s_in, s_out, order, dtype, groups, extra flags
     ("gcn", "sbm1500", 100, 256, "agg", "f32", 1, 0),
     ("gcn", "cl2000", 300, 64, "xform", "f32", 1, 0),      # dH from the GEMM
-    ("gcn", "sbm1500", 700, 96, "xform", "f32", 1, 0),     # stream-K dH product + fix-up
+    ("gcn", "sbm1500", 700, 96, "xform", "f32", 1, 0),     # ragged tile columns
     ("sage", "sbm1500", 128, 96, "agg", "f32", 1, 0),      # Add aliases the output
     ("sage", "sbm1100", 1024, 1024, "agg", "f32", 1, 0),
     ("gcn", "sbm1500", 64, 48, "agg", "f32", 3, 0),        # grouped, aggregate first
     ("gcn", "sbm1500", 96, 32, "xform", "f32", 3, 0),      # grouped, transform first
     ("sage", "sbm1500", 512, 512, "agg", "bf16", 1, 0),
-    ("gcn", "cl2000", 1024, 512, "xform", "bf16", 1, 0),   # packed bf16 dH product
+    ("gcn", "cl2000", 1024, 512, "xform", "bf16", 1, 0),   # bf16 dH product
     ("gcn", "sbm1500", 100, 64, "agg", "bf16", 1, 0),
     ("sage", "sbm1500", 128, 96, "agg", "f32", 1, 4),      # matrix-core aggregation
     ("gcn", "rect", 80, 40, "xform", "f32", 1, 0),         # rectangular (layer-sampled)

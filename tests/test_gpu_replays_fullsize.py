@@ -5,7 +5,7 @@ cluster mini-batches, m = 4) and c7 (GIST + LADIES, 512 outputs and 512
 draws per layer) with every sub-GCN step replayed from a HIP graph at
 padded capacity shapes.  Here the benchmark's round workload runs two
 rounds that way and, on a second instance, kernel by kernel; after subAgg
-the global models agree within 1e-5 (the padded shapes move stream-K split
+the global models agree within 1e-5 (the padded shapes move the products' K cut
 points, so the sums differ by rounding only), and both moved away from the
 initial weights.
 """

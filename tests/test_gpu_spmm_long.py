@@ -1,4 +1,4 @@
-"""Aggregation with hub rows: rows longer than 128 entries of a sparse matrix are shared by the
+"""Aggregation with hub rows: rows longer than 128 entries are summed in 16 parts, shared by the
 waves of a block (wide features) or the lane groups of a wave (narrow ones).
 
 The sum of a row of k entries in any order has error <= (k + 1) 2^-24 sum |a||x|."""
