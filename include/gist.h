@@ -312,7 +312,9 @@ enum {
  * 34 against 55 us for a 10-cluster mini-batch at width 4,096); without the
  * structure it gathers every entry and is slower. */
 
-/* Workspace (device bytes) that fwd and bwd need for this descriptor. */
+/* Workspace (device bytes) that fwd and bwd need for this descriptor: the
+ * intermediate tensors (a transform-first product; dZ and dP) and at most
+ * 256 MiB of partial sums of the dense products. */
 gist_status gist_layer_workspace_size(const gist_layer_desc* L, size_t* fwd_bytes,
                                       size_t* bwd_bytes);
 

@@ -23,13 +23,15 @@
 // in registers on the way to LDS, so every value is split once per tile that
 // uses it and memory sees the fp32 operands only.
 //
-// What bounds it: power.  A loop of nothing but these MFMAs on random data
-// holds 1,720 TFLOP/s (287 of fp32 products) at 1.8 GHz, on zeros 2,440; the
-// 256 x 256 tiles keep the matrix cores busy 72% of the cycles at 1.77 GHz.
-// On the products of a 4,096-wide GraphSAGE layer with 1,630 nodes (109 GFLOP
-// each), the fp32 matrix instruction took 985 / 985 / 950 us (forward, dH,
-// dW; back to back, hot) and this 620 / 610 / 600; for 512 x 512 weights
-// and 20,000 nodes 134 -> 83 us; a 1,536 x 64 product over K = 602 27 -> 11.
+// What bounds it: power, and beside it the vector unit (splitting, and the
+// additions of gemm_split_kernel).  A loop of nothing but these MFMAs on random
+// data holds 1,720 TFLOP/s (287 of fp32 products) at 1.8 GHz, on zeros 2,440; the
+// 256 x 256 tiles keep the matrix cores busy 55-58% of the cycles, the
+// 128 x 128 ones 63%.  On the products of a 4,096-wide GraphSAGE layer with 1,630
+// nodes (109 GFLOP each), the fp32 matrix instruction took 985 / 985 / 950 us
+// (forward, dH, dW; back to back, hot: between other kernels all of these are
+// 5-10% less) and this 605 / 590 / 555; for 512 x 512 weights and 20,000 nodes
+// 134 -> 85; a 1,536 x 64 product over K = 602 27 -> 11.
 //
 // Non-finite and huge values: the split of an Inf or NaN, or of a value that is
 // Inf in bf16 when scaled (from 2^104 on), leaves NaN in the tile, and sums
@@ -506,7 +508,10 @@ __device__ __forceinline__ void store_part(const floatx16 (&acc)[WM][WN], float 
 // buffers of 6 bytes per value (144 KB at 256 x 256).  Larger tiles halve the
 // splitting work and LDS traffic per MFMA (105 VALU for it to 48 MFMAs per wave
 // and step at 256 x 256, twice that at 128 x 128), which is what is left of
-// the power for the matrix cores.
+// the power for the matrix cores.  Both use all 256 registers of two waves per
+// SIMD: the compiler spills 20 to 110 vector registers around the main loop
+// (the prologue and the epilogue), at most one access in it, and some 150
+// scalar ones (the arguments) to vector lanes.
 template <int WM, int WN, int NWM, int NWN, bool AK, bool BK, int V>
 __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
     int64_t M, int64_t N, int64_t K, int64_t msplit, int64_t ksplit, SOp A, SOp B, SOut C, SSched S,
@@ -926,7 +931,8 @@ __global__ __launch_bounds__(256, WM == 1 ? 3 : 2) void gemm_small_kernel(
 // row-contiguous operand dW took 190 us instead of 156, with the two 16-byte
 // halves of a lane's 32 bytes in turn (half lines) dH 167 instead of 150.
 // On a 4,096-wide GraphSAGE layer with 1,630 nodes (109 GFLOP each; forward,
-// dH, dW): 209 / 167 / 206 us -> 202 / 150 / 156; four sub-GCNs' 3,100 x 1,024
+// dH, dW; back to back, hot): 209 / 167 / 206 us -> 202 / 150 / 156 (in a training
+// round 165 / 141 / 158); four sub-GCNs' 3,100 x 1,024
 // products over K = 2,048 in one grid instead of four: 340 -> 85 us.
 constexpr int KB = 32;
 template <bool AK, bool BK, int V>
@@ -1168,13 +1174,14 @@ struct Cfg {
   double fixed_us;    // a workgroup's first loads and its stores
 };
 // 0..2: fp32; 3..5: bf16 inputs.  The times were measured with the machine full
-// (256 x 256: 102 steps over 512 tiles in 630 us; 128 x 128: 102 steps over
-// 2,048 tiles in 658; 64 x 64: 8 steps over 2,504 tiles in 112) and nearly
+// (256 x 256: 102 steps over 512 tiles in 550 us; 128 x 128: 102 steps over
+// 2,048 tiles in 640; 64 x 64: 8 steps over 2,504 tiles in 112) and nearly
 // empty; choose_cfg takes the shape whose estimate is lowest.  Where two
-// are close: 3,100 x 1,024 over K = 1,204 takes 72.0 / 72.6 / 89 us with the
-// three fp32 tiles, 1,630 x 8,192 over K = 47 24 / 30 / 42, 2,000 x 128 over
-// K = 1,433 32 / 21 / 23, 3,100 x 64 over K = 602 35 / 21 / 12.
-constexpr Cfg kCfg[] = {{256, 256, KS, 1, 8, kRunK / KS, 2.95, 1.75, 14.0},
+// are close: 300,000 x 256 over K = 256 takes 292 / 284 us with the two large
+// fp32 tiles, 2,048 x 2,048 over K = 8,192 352 / 394; 3,100 x 1,024 over K = 1,204
+// 72 / 73 / 89 with all three, 1,630 x 8,192 over K = 47 24 / 30 / 42, 2,000 x 128
+// over K = 1,433 32 / 21 / 23, 3,100 x 64 over K = 602 35 / 21 / 12.
+constexpr Cfg kCfg[] = {{256, 256, KS, 1, 8, kRunK / KS, 2.8, 1.65, 14.0},
                         {128, 128, KS, 2, 8, kRunK / KS, 1.5, 0.8, 7.0},
                         {64, 64, KL, 3, 2, kRunK / KL, 3.5, 1.0, 4.0},
                         {128, 128, 64, 2, 2, 1 << 20, 2.0, 1.0, 7.0},
