@@ -397,27 +397,39 @@ __device__ __forceinline__ void recompute(floatx16 (&acc)[WM][WN], const SSched&
     k_step<KW>(S, K, ksplit, j, k0, klim, second);
     const float* pa = AK ? (second ? a1 + (k0 - ksplit) : a0 + k0) : a0 + k0 * lda;
     const float* pb = BK ? b0 + k0 : b0 + k0 * ldb;
-    for (int kk = 0; kk < klim; kk += 2) {
-      const int k = min(kk + lh, klim - 1);
-      const bool in = kk + lh < klim;
-      float x[WM], y[WN];
+    // Eight values of K at a time, four for each half of the wave.  (No faster
+    // than two at a time, but the compiler then spills 32 instead of 112 vector
+    // registers around the main loop of the 256 x 256 K x row-contiguous form.)
+    for (int kk = 0; kk < klim; kk += 8) {
+      float x[WM][4], y[WN][4];
 #pragma unroll
       for (int a = 0; a < WM; ++a) {
         const int64_t r = min<int64_t>(wr + a * 32 + li, rows_left - 1);
-        const float e = AK ? pa[r * lda + k] : pa[k * lda + r];
-        x[a] = in ? e : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int k = min(kk + 4 * lh + i, klim - 1);
+          x[a][i] = AK ? pa[r * lda + k] : pa[k * lda + r];
+        }
       }
 #pragma unroll
       for (int b = 0; b < WN; ++b) {
         const int64_t r = min<int64_t>(wc + b * 32 + li, cols_left - 1);
-        const float e = BK ? pb[r * ldb + k] : pb[k * ldb + r];
-        y[b] = in ? e : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int k = min(kk + 4 * lh + i, klim - 1);
+          y[b][i] = BK ? pb[r * ldb + k] : pb[k * ldb + r];
+        }
       }
 #pragma unroll
-      for (int a = 0; a < WM; ++a)
+      for (int i = 0; i < 4; ++i) {
+        const bool in = kk + 4 * lh + i < klim;
 #pragma unroll
-        for (int b = 0; b < WN; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[a], y[b], acc[a][b], 0, 0, 0);
+        for (int a = 0; a < WM; ++a)
+#pragma unroll
+          for (int b = 0; b < WN; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? x[a][i] : 0.f, in ? y[b][i] : 0.f, acc[a][b],
+                                                             0, 0, 0);
+      }
     }
   }
 }
@@ -509,7 +521,7 @@ __device__ __forceinline__ void store_part(const floatx16 (&acc)[WM][WN], float 
 // splitting work and LDS traffic per MFMA (105 VALU for it to 48 MFMAs per wave
 // and step at 256 x 256, twice that at 128 x 128), which is what is left of
 // the power for the matrix cores.  Both use all 256 registers of two waves per
-// SIMD: the compiler spills 20 to 110 vector registers around the main loop
+// SIMD: the compiler spills 20 to 40 vector registers around the main loop
 // (the prologue and the epilogue), at most one access in it, and some 150
 // scalar ones (the arguments) to vector lanes.
 template <int WM, int WN, int NWM, int NWN, bool AK, bool BK, int V>

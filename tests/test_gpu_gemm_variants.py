@@ -23,24 +23,25 @@ CASES = [
     ("gcn", 1304, 20, 3168, 3, 0, 0, 0, 1, "KK_64x64_v44 KR_256x256_v44 RR_64x64_v44"),
     ("sage", 2, 3008, 4, 1, 0, 0, 2, 1, "KK_64x64_v22 KR_64x64_v44 RR_64x64_v22"),
     ("sage", 3, 93, 4289, 3, 0, 0, 0, 0, "KK_64x64_v11 KR_64x64_v11 RR_128x128_v11"),
-    ("sage", 3, 1846, 3826, 1, 0, 0, 0, 0, "KK_64x64_v22 KR_64x64_v22 RR_256x256_v22"),
     ("sage", 91, 2744, 2432, 1, 0, 0, 0, 0, "KK_128x128_v44 KR_128x128_v44 RR_256x256_v44"),
     ("sage", 98, 1274, 2491, 2, 0, 0, 2, 1, "KK_128x128_v11 KR_128x128_v11 RR_256x256_v11"),
+    ("sage", 400, 3840, 3840, 1, 0, 2, 0, 0, "KK_128x128_v22 KR_128x128_v22 RR_256x256_v44"),
     ("sage", 555, 64, 8, 1, 0, 0, 1, 0, "KK_64x64_v14 KR_64x64_v44 RR_64x64_v41"),
     ("sage", 718, 4236, 2, 1, 0, 0, 1, 0, "KK_128x128_v11 KR_64x64_v22 RR_64x64_v41"),
-    ("sage", 1630, 4096, 4096, 1, 0, 2, 0, 1, "KK_128x128_v22 KR_256x256_v22 RR_256x256_v44"),
+    ("sage", 1274, 1724, 3766, 2, 0, 0, 0, 0, "KK_128x128_v22 KR_256x256_v22 RR_256x256_v22"),
     ("sage", 1686, 64, 2554, 2, 0, 2, 0, 0, "KK_64x64_v22 KR_128x128_v22 RR_64x64_v22"),
     ("sage", 1784, 1342, 5, 3, 0, 0, 1, 1, "KK_256x256_v11 KR_64x64_v11 RR_64x64_v11"),
     ("sage", 2407, 256, 1672, 3, 0, 2, 1, 1, "KK_128x128_v11 KR_256x256_v22 RR_128x128_v11"),
-    ("sage", 3690, 3924, 1155, 1, 0, 1, 2, 1, "KK_128x128_v11 KR_256x256_v11 RR_128x128_v11"),
+    ("sage", 3196, 3584, 2478, 1, 0, 1, 2, 1, "KK_128x128_v11 KR_256x256_v11 RR_256x256_v22"),
+    ("sage", 3778, 3422, 1210, 1, 0, 0, 1, 0, "KK_256x256_v11 KR_256x256_v22 RR_128x128_v11"),
     ("sage", 3840, 3840, 400, 1, 0, 2, 0, 1, "KK_256x256_v22 KR_128x128_v22 RR_128x128_v44"),
     ("sage", 4034, 4, 1136, 3, 0, 1, 0, 1, "KK_64x64_v41 KR_256x256_v11 RR_64x64_v44"),
     ("sage", 4260, 126, 746, 2, 0, 0, 0, 1, "KK_128x128_v22 KR_128x128_v22 RR_128x128_v22"),
     ("xform", 2, 484, 2160, 3, 0, 1, 0, 1, "KK_64x64_v41 KR_64x64_v41 RR_128x128_v44"),
     ("xform", 552, 3, 16, 2, 0, 0, 2, 0, "KK_64x64_v44 KR_64x64_v14 RR_64x64_v14"),
     ("xform", 1374, 2494, 3, 1, 0, 0, 0, 0, "KK_128x128_v11 KR_64x64_v11 RR_64x64_v11"),
+    ("xform", 1672, 3210, 2536, 3, 0, 2, 0, 0, "KK_256x256_v22 KR_256x256_v22 RR_256x256_v22"),
     ("xform", 1972, 3856, 4, 2, 0, 0, 0, 1, "KK_256x256_v44 KR_64x64_v44 RR_64x64_v44"),
-    ("xform", 2245, 2288, 4104, 2, 0, 1, 1, 1, "KK_256x256_v11 KR_128x128_v11 RR_128x128_v44"),
     ("xform", 3340, 102, 1280, 3, 0, 0, 0, 0, "KK_128x128_v44 KR_256x256_v22 RR_128x128_v22"),
     ("sage", 5, 4, 3, 1, 1, 1, 1, 0, "KK_64x64_v11 KR_64x64_v41 RR_64x64_v41"),
     ("sage", 18, 64, 4, 1, 1, 0, 1, 0, "KK_64x64_v14 KR_64x64_v44 RR_64x64_v41"),
