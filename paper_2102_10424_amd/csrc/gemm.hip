@@ -522,7 +522,7 @@ __device__ __forceinline__ void store_part(const floatx16 (&acc)[WM][WN], float 
 // and step at 256 x 256, twice that at 128 x 128), which is what is left of
 // the power for the matrix cores.  Both use all 256 registers of two waves per
 // SIMD: the compiler spills 20 to 40 vector registers around the main loop
-// (the prologue and the epilogue), at most one access in it, and some 150
+// (the prologue and the epilogue), up to three accesses in it, and some 150
 // scalar ones (the arguments) to vector lanes.
 template <int WM, int WN, int NWM, int NWN, bool AK, bool BK, int V>
 __global__ __launch_bounds__(64 * NWM * NWN, 2) void gemm_split_kernel(
@@ -1202,11 +1202,11 @@ constexpr Cfg kCfg[] = {{256, 256, KS, 1, 8, kRunK / KS, 2.8, 1.65, 14.0},
 constexpr int64_t kCUs = 256;
 constexpr unsigned threads_of(const Cfg& c) { return c.bm == 256 ? 512 : 256; }
 constexpr int64_t kMaxLd = int64_t(1) << 22;   // 255 rows of it in 32 bits of bytes
-// Parts of at most 4,096 values of K round less than longer ones (a weight
-// gradient over 2.45M nodes: see the runs' bound in make_ssched) but number
-// M N K / 4,096, twice the output and more for a product that has tiles enough:
-// 80 GB for 2.45M x 4,096 over K = 8,192.  Beyond this much workspace K is cut
-// only as far as the machine has to be filled (at most three parts per slot).
+// Parts of at most 4,096 values of K round less than longer ones, but hold
+// M N K / 4,096 sums, twice the output and more for a product that has tiles
+// enough: 80 GB for 2.45M x 4,096 over K = 8,192.  Beyond this much workspace K is
+// cut only as far as the machine has to be filled (at most three parts for
+// each workgroup it holds).
 constexpr int64_t kMaxPartBytes = int64_t(256) << 20;
 
 // Time of `units` workgroups of `steps` steps: whole rounds of full CUs,
